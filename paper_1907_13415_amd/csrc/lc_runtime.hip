@@ -284,25 +284,82 @@ static lc_status run_steps_staged(lc_ctx* c, int64_t n) {
 }
 
 
+// Planes per block along z for a sweep of `tiles` column tiles on a grid of
+// nz planes, at most `most`.  A block of zc planes marches zc + `extra`
+// planes, one after another, so a grid with few tiles is bound by that serial
+// chain while most CUs idle: there shorter chunks win in spite of the planes
+// they compute twice.  The estimate counts, per CU, the marches that run one
+// after another; with two blocks resident (nearly every form of the sweeps) a
+// march beside another on its CU takes 1.4 times as long as alone (measured
+// 1.3-1.6).
+// Measured on the stress/LB and Q sweeps, long default chunks against the
+// chosen ones: 24^3 FP32 67.7 -> 14.7 and 56.9 -> 11.7 us, 64^3 FP64
+// 80 -> 32 and 147 -> 24 us, 129x100x75 FP32 isotropic 186 -> 95 and
+// 474 -> 111 us; from 256^3 on the chunk is the longest allowed.
+static int pick_chunk(int nz, int64_t tiles, int most, int extra, int resident = 2) {
+  constexpr int CUS = 256;
+  constexpr double BESIDE = 1.4;
+  int best = 1;
+  double best_cost = 1e300;
+  for (int zc = 1; zc <= std::min(most, nz); zc++) {
+    const int64_t blocks = tiles * ((nz + zc - 1) / zc);
+    const int64_t full = blocks / (CUS * resident), rest = blocks % (CUS * resident);
+    const double together = resident == 1 ? 1.0 : BESIDE;
+    const double rounds = double(full) * together + (rest == 0 ? 0.0 : (rest <= CUS ? 1.0 : together));
+    const double cost = rounds * (zc + extra);
+    if (cost <= best_cost) {
+      best_cost = cost;
+      best = zc;
+    }
+  }
+  return best;
+}
+
+// Chunks of the two sweeps (planes per block along z).
+struct Chunks {
+  int lb, q;
+};
+
+// Tiles of the stress/LB sweep with the isotropic stencils, whose stress
+// ring of three planes (3D) leaves room for two blocks per CU: 32x8 (float),
+// 16x8 (double in 3D).
+template <int LAT, typename S>
+constexpr int iso_lb_tx() {
+  return (Lattice<LAT>::dim == 3 && sizeof(S) == 8) ? 16 : 32;
+}
+constexpr int ISO_LB_TY = 8;
+
+// The chunks of the context's steps: as set by lc_set_chunk, else by
+// pick_chunk (once per call, not per step).  Chunks longer than the grid are
+// the whole depth (the block index arithmetic stays within int).
+template <int LAT, typename S, typename QT>
+static Chunks split_chunks(const lc_ctx* c) {
+  using C = SplitCfg<LAT, QT, S>;
+  if constexpr (!C::d3) return Chunks{1, 1};
+  if (c->zchunk > 0) return Chunks{std::min(c->zchunk, c->g.nz), std::min(c->zchunk, c->g.nz)};
+  auto tiles = [&](int tx, int ty) { return int64_t((c->g.nx + tx - 1) / tx) * ((c->g.ny + ty - 1) / ty); };
+  const bool iso = c->stencil == LC_STENCIL_ISOTROPIC;
+  // MRT and the isotropic stencils march up to 32 planes in the float
+  // stress/LB sweep (1% and 3% faster there than 16 on large grids)
+  const bool wide = sizeof(S) == 4 && (c->coll == LC_COLL_MRT || iso);
+  return Chunks{pick_chunk(c->g.nz, iso ? tiles(iso_lb_tx<LAT, S>(), ISO_LB_TY) : tiles(C::LB_TX, C::LB_TY),
+                           wide ? 32 : C::ZC_LB, 2),
+                pick_chunk(c->g.nz, tiles(C::Q_TX, C::Q_TY), C::ZC_Q, 2)};
+}
+
 // One step of the split sweeps between explicit buffers (pull-form
 // populations) on stream st; u receives the force-corrected velocity.
 // rec_lb / rec_q, when not null, record rho and F / the predictor for
 // reverse-mode replay.  With mark, timing events bracket the two sweeps.
 template <int LAT, typename S, bool DEV, typename QT = S>
-static void step_split_ptrs(lc_ctx* c, hipStream_t st, bool mark, const S* f0, const QT* q0, S* f1, QT* q1, QT* u,
-                            S* rec_lb, QT* rec_q) {
+static void step_split_ptrs(lc_ctx* c, hipStream_t st, bool mark, const Chunks& z, const S* f0, const QT* q0, S* f1,
+                            QT* q1, QT* u, S* rec_lb, QT* rec_q) {
   // tile shapes of the order-tensor type, whose LDS regions dominate
   using C = SplitCfg<LAT, QT, S>;
   const GridDims gd{c->g.nx, c->g.ny, c->g.nz, c->L.N};
   const Coef<S> k = ctx_coef<S>(c);
   const Coef<QT> kq = ctx_coef<QT>(c);
-  // MRT and the isotropic stencils march 32-plane chunks in the float
-  // stress/LB sweep (1% and 3% faster there than 16)
-  const bool wide = sizeof(S) == 4 && (c->coll == LC_COLL_MRT || c->stencil == LC_STENCIL_ISOTROPIC);
-  // chunks longer than the grid are the whole depth (the block index
-  // arithmetic stays within int)
-  const int zc1 = C::d3 ? std::min(c->zchunk > 0 ? c->zchunk : (wide ? 32 : C::ZC_LB), c->g.nz) : 1;
-  const int zc2 = C::d3 ? std::min(c->zchunk > 0 ? c->zchunk : C::ZC_Q, c->g.nz) : 1;
+  const int zc1 = z.lb, zc2 = z.q;
   const dim3 g1((c->g.nx + C::LB_TX - 1) / C::LB_TX, (c->g.ny + C::LB_TY - 1) / C::LB_TY,
                 unsigned((c->g.nz + zc1 - 1) / zc1));
   const dim3 g2((c->g.nx + C::Q_TX - 1) / C::Q_TX, (c->g.ny + C::Q_TY - 1) / C::Q_TY,
@@ -310,9 +367,7 @@ static void step_split_ptrs(lc_ctx* c, hipStream_t st, bool mark, const S* f0, c
   hipEvent_t e = mark ? ctx_begin(c, st) : nullptr;
   if constexpr (std::is_same<S, QT>::value) {
     if (c->stencil == LC_STENCIL_ISOTROPIC) {  // the sweeps with the isotropic stencils
-      // stress/LB tiles whose stress ring of three planes (3D) leaves room
-      // for two blocks per CU: 32x8 (float), 16x8 (double in 3D)
-      constexpr int ITX = (C::d3 && sizeof(S) == 8) ? 16 : 32, ITY = 8;
+      constexpr int ITX = iso_lb_tx<LAT, S>(), ITY = ISO_LB_TY;
       const dim3 gi((c->g.nx + ITX - 1) / ITX, (c->g.ny + ITY - 1) / ITY, unsigned((c->g.nz + zc1 - 1) / zc1));
       if (c->coll == LC_COLL_MRT)
         hipLaunchKernelGGL((split_lb<LAT, S, DEV, ITX, ITY, 1, true, QT, STENCIL_ISO>), gi, dim3(ITX, ITY), 0, st, q0,
@@ -396,7 +451,8 @@ static void step_fused_ptrs(lc_ctx* c, hipStream_t st, bool mark, const S* f0, c
   using C = FusedCfg<LAT, QT>;
   hipEvent_t e = mark ? ctx_begin(c, st) : nullptr;
   if constexpr (C::d3) {
-    const int zc = std::min(c->zchunk > 0 ? c->zchunk : C::ZC, c->g.nz);
+    const int64_t tiles = int64_t((c->g.nx + C::TX - 1) / C::TX) * ((c->g.ny + C::TY - 1) / C::TY);
+    const int zc = c->zchunk > 0 ? std::min(c->zchunk, c->g.nz) : pick_chunk(c->g.nz, tiles, C::ZC, 8, 1);
     launch_fused<LAT, S, DEV, QT, C::TX, C::TY, C::NTHR>(c, st, zc, f0, q0, f1, q1);
   } else {
     auto tiles = [&](int tx, int ty) { return int64_t((c->g.nx + tx - 1) / tx) * ((c->g.ny + ty - 1) / ty); };
@@ -427,8 +483,9 @@ static lc_status run_steps_fused(lc_ctx* c, int64_t n) {
 template <int LAT, typename S, bool DEV, typename QT = S>
 static lc_status run_steps_split(lc_ctx* c, int64_t n) {
   QT* u = reinterpret_cast<QT*>(static_cast<char*>(c->b.scratch) + c->L.off_u);
+  const Chunks z = split_chunks<LAT, S, QT>(c);
   for (int64_t it = 0; it < n; it++) {
-    step_split_ptrs<LAT, S, DEV, QT>(c, c->stream, true, static_cast<const S*>(c->b.f[c->parity]),
+    step_split_ptrs<LAT, S, DEV, QT>(c, c->stream, true, z, static_cast<const S*>(c->b.f[c->parity]),
                                      static_cast<const QT*>(c->b.Q[c->parity]),
                                      static_cast<S*>(c->b.f[c->parity ^ 1]), static_cast<QT*>(c->b.Q[c->parity ^ 1]),
                                      u, nullptr, nullptr);
@@ -910,7 +967,7 @@ static void vjp_replay(lc_ctx* c, hipStream_t st, const double* f_ck, const doub
   hipLaunchKernelGGL((load_state<0, double, false>), site_grid(c->g), site_block(), 0, st, f_ck, q_ck, H.f(0),
                      H.q(0), gd);
   for (int j = 0; j < n; j++)
-    step_split_ptrs<0, double, false>(c, st, false, H.f(j), H.q(j), H.f(j + 1), H.q(j + 1), H.u(j), H.r(j), H.p(j));
+    step_split_ptrs<0, double, false>(c, st, false, Chunks{1, 1}, H.f(j), H.q(j), H.f(j + 1), H.q(j + 1), H.u(j), H.r(j), H.p(j));
 }
 
 // The reverse steps n-1 .. 0 of a recorded segment on the context stream.
@@ -1108,8 +1165,9 @@ static size_t static_velocity_bytes(const lc_grid& g) {
 template <int LAT, typename S, bool DEV, typename QT = S>
 static lc_status run_static(lc_ctx* c, void* u_dev, int64_t n) {
   QT* u = static_cast<QT*>(u_dev);
+  const Chunks z = split_chunks<LAT, S, QT>(c);
   for (int64_t it = 0; it < n; it++) {
-    step_split_ptrs<LAT, S, DEV, QT>(c, c->stream, false, static_cast<const S*>(c->b.f[c->parity]),
+    step_split_ptrs<LAT, S, DEV, QT>(c, c->stream, false, z, static_cast<const S*>(c->b.f[c->parity]),
                                      static_cast<const QT*>(c->b.Q[c->parity]),
                                      static_cast<S*>(c->b.f[c->parity ^ 1]), static_cast<QT*>(c->b.Q[c->parity ^ 1]),
                                      u, nullptr, nullptr);
