@@ -327,52 +327,77 @@ LC_HD void stress_col(const Sym<T>& Q, const Sym<T>& H, const Sym<T> (&dQ)[3], c
 // With RAW set, dQ and G are undivided central differences (twice the
 // derivatives) and u is halved: the same rate up to rounding (the factors
 // of two are exact), with the halvings saved.
-template <typename T>
+// DIM = 2: u_z and every derivative along z are zero and their terms are left
+// out (they would be fused multiply-adds that add an exact zero, which the
+// compiler may not drop by itself: a third of the rate's instructions).
+template <typename T, int DIM = 3>
 struct Flow {
-  T u[3];
-  T B[3][3];
-  T g[5];
+  T u[DIM];
+  T B[DIM][DIM];
+  T g[DIM == 3 ? 5 : 3];
 };
 
-template <typename T, bool RAW = false>
-LC_HD Flow<T> flow_terms(const T (&u)[3], const T (&G)[3][3], const Coef<T>& c) {
-  Flow<T> f;
+template <typename T, bool RAW = false, int DIM = 3>
+LC_HD Flow<T, DIM> flow_terms(const T (&u)[3], const T (&G)[3][3], const Coef<T>& c) {
+  Flow<T, DIM> f;
   const T xp = RAW ? c.xi_p * T(0.5) : c.xi_p, xm = RAW ? c.xi_m * T(0.5) : c.xi_m;
 #pragma unroll
-  for (int a = 0; a < 3; a++) {
+  for (int a = 0; a < DIM; a++) {
     f.u[a] = u[a];
 #pragma unroll
-    for (int b = 0; b < 3; b++) f.B[a][b] = xp * G[a][b] + xm * G[b][a];
+    for (int b = 0; b < DIM; b++) f.B[a][b] = xp * G[a][b] + xm * G[b][a];
   }
-  f.g[0] = G[0][0] - G[2][2];
-  f.g[1] = G[1][1] - G[2][2];
-  f.g[2] = G[0][1] + G[1][0];
-  f.g[3] = G[0][2] + G[2][0];
-  f.g[4] = G[1][2] + G[2][1];
+  if constexpr (DIM == 3) {
+    f.g[0] = G[0][0] - G[2][2];
+    f.g[1] = G[1][1] - G[2][2];
+    f.g[2] = G[0][1] + G[1][0];
+    f.g[3] = G[0][2] + G[2][0];
+    f.g[4] = G[1][2] + G[2][1];
+  } else {
+    f.g[0] = G[0][0];
+    f.g[1] = G[1][1];
+    f.g[2] = G[0][1] + G[1][0];
+  }
   return f;
 }
 
-template <typename T, bool RAW = false>
-LC_HD Sym<T> be_rate_flow(const Sym<T>& Q, const Sym<T>& H, const Sym<T> (&dQ)[3], const Flow<T>& f,
+template <typename T, bool RAW = false, int DIM = 3>
+LC_HD Sym<T> be_rate_flow(const Sym<T>& Q, const Sym<T>& H, const Sym<T> (&dQ)[3], const Flow<T, DIM>& f,
                           const Coef<T>& c) {
   const T Qp[3][3] = {{Q.xx + T(1.0 / 3.0), Q.xy, Q.xz},
                       {Q.xy, Q.yy + T(1.0 / 3.0), Q.yz},
                       {Q.xz, Q.yz, Q.zz() + T(1.0 / 3.0)}};
   // S_ab = A_ab + A_ba with A = B Qp.  Each component is accumulated as one
   // chain of fused multiply-adds, starting from the advection term.
-  const T qg = Q.xx * f.g[0] + Q.yy * f.g[1] + Q.xy * f.g[2] + Q.xz * f.g[3] + Q.yz * f.g[4];
+  T qg;
+  if constexpr (DIM == 3)
+    qg = Q.xx * f.g[0] + Q.yy * f.g[1] + Q.xy * f.g[2] + Q.xz * f.g[3] + Q.yz * f.g[4];
+  else
+    qg = Q.xx * f.g[0] + Q.yy * f.g[1] + Q.xy * f.g[2];
   const T k = RAW ? c.xi * qg : T(2) * c.xi * qg;
-  const T(&u)[3] = f.u;
   // -(u . grad) of one component, then - k Qp_ab
-  auto base = [&](T d0, T d1, T d2, T qp) { return -(u[0] * d0) - (u[1] * d1 + (u[2] * d2 + k * qp)); };
+  auto base = [&](T d0, T d1, T d2, T qp) {
+    if constexpr (DIM == 3)
+      return -(f.u[0] * d0) - (f.u[1] * d1 + (f.u[2] * d2 + k * qp));
+    else
+      return -(f.u[0] * d0) - (f.u[1] * d1 + k * qp);
+  };
   // sum_g B_ag Qp_gb + B_bg Qp_ga added to x
   auto sym = [&](int a, int b, T x) {
-    return f.B[a][0] * Qp[0][b] + (f.B[a][1] * Qp[1][b] + (f.B[a][2] * Qp[2][b] +
-           (f.B[b][0] * Qp[0][a] + (f.B[b][1] * Qp[1][a] + (f.B[b][2] * Qp[2][a] + x)))));
+    if (b < DIM) {
+#pragma unroll
+      for (int g = DIM - 1; g >= 0; g--) x = f.B[b < DIM ? b : 0][g] * Qp[g][a] + x;
+    }
+#pragma unroll
+    for (int g = DIM - 1; g >= 0; g--) x = f.B[a][g] * Qp[g][b] + x;
+    return x;
   };
   // 2 A_aa added to x
   auto diag = [&](int a, T x) {
-    return T(2) * (f.B[a][0] * Qp[0][a] + f.B[a][1] * Qp[1][a] + f.B[a][2] * Qp[2][a]) + x;
+    if constexpr (DIM == 3)
+      return T(2) * (f.B[a][0] * Qp[0][a] + f.B[a][1] * Qp[1][a] + f.B[a][2] * Qp[2][a]) + x;
+    else
+      return T(2) * (f.B[a][0] * Qp[0][a] + f.B[a][1] * Qp[1][a]) + x;
   };
   Sym<T> R;
   R.xx = c.Gam * H.xx + diag(0, base(dQ[0].xx, dQ[1].xx, dQ[2].xx, Qp[0][0]));

@@ -151,33 +151,42 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
   constexpr int P4 = (R4::N + NTHR - 1) / NTHR, P2 = (R2::N + NTHR - 1) / NTHR;
   const uint32_t sy = uint32_t(g.nx), sz = uint32_t(g.nx) * uint32_t(g.ny);
   uint32_t q_off[P4];
-#pragma unroll
-  for (int n = 0; n < P4; n++) {
-    const int k = tid + n * NTHR;
-    const int i = k % R4::W, j = k / R4::W;
-    q_off[n] = k < R4::N ? uint32_t(wrapi(x0 - 4 + i, g.nx)) + sy * uint32_t(wrapi(y0 - 4 + j, g.ny)) : 0u;
-  }
   struct InPlane {
     uint32_t s, xp, xm, yp, ym;
   };
   InPlane ip[P2];
+  auto in_plane = [&](auto wrap) {
 #pragma unroll
-  for (int n = 0; n < P2; n++) {
-    const int k = tid + n * NTHR;
-    int i2 = 0, j2 = 0;
-    if (k < R2::N) tile_first<TX, TY, 2>(k, i2, j2);
-    const int gx = wrapi(x0 - 2 + i2, g.nx), gy = wrapi(y0 - 2 + j2, g.ny);
-    ip[n].s = uint32_t(gx) + sy * uint32_t(gy);
-    ip[n].xp = (gx + 1 == g.nx) ? 0u - uint32_t(g.nx - 1) : 1u;
-    ip[n].xm = (gx == 0) ? uint32_t(g.nx - 1) : 0u - 1u;
-    ip[n].yp = (gy + 1 == g.ny) ? 0u - uint32_t(g.ny - 1) * sy : sy;
-    ip[n].ym = (gy == 0) ? uint32_t(g.ny - 1) * sy : 0u - sy;
-  }
+    for (int n = 0; n < P4; n++) {
+      const int k = tid + n * NTHR;
+      const int i = k % R4::W, j = k / R4::W;
+      q_off[n] = k < R4::N ? uint32_t(wrap(x0 - 4 + i, g.nx)) + sy * uint32_t(wrap(y0 - 4 + j, g.ny)) : 0u;
+    }
+#pragma unroll
+    for (int n = 0; n < P2; n++) {
+      const int k = tid + n * NTHR;
+      int i2 = 0, j2 = 0;
+      if (k < R2::N) tile_first<TX, TY, 2>(k, i2, j2);
+      const int gx = wrap(x0 - 2 + i2, g.nx), gy = wrap(y0 - 2 + j2, g.ny);
+      ip[n].s = uint32_t(gx) + sy * uint32_t(gy);
+      ip[n].xp = (gx + 1 == g.nx) ? 0u - uint32_t(g.nx - 1) : 1u;
+      ip[n].xm = (gx == 0) ? uint32_t(g.nx - 1) : 0u - 1u;
+      ip[n].yp = (gy + 1 == g.ny) ? 0u - uint32_t(g.ny - 1) * sy : sy;
+      ip[n].ym = (gy == 0) ? uint32_t(g.ny - 1) * sy : 0u - sy;
+    }
+  };
+  // without a division where the rectangle wraps at most once
+  if (g.nx >= R4::W && g.ny >= R4::H)
+    in_plane([](int v, int n) { return wrap_near(v, n); });
+  else
+    in_plane([](int v, int n) { return wrapi(v, n); });
 
-  // Register staging of the next plane's global loads (float forms in 3D,
-  // where registers allow): the Q rectangle of plane p+1 and the populations
-  // of the next moment plane are in flight while the stages of plane p run.
-  constexpr bool PF = DIM == 3 && sizeof(QT) == 4;
+  // Register staging of the global loads: in 3D (float forms, where registers
+  // allow) the Q rectangle of plane p+1 and the populations of the next
+  // moment plane are in flight while the stages of plane p run; in 2D every
+  // load of the block is issued before the first stage, so a step waits for
+  // memory once and not once per stage that reads it.
+  constexpr bool PF = DIM == 2 || sizeof(QT) == 4;
   struct QRegs {
     QT v[PF ? P4 : 1][5];
   };
@@ -376,7 +385,7 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
   // quantities the two-sweep Q update keeps).
   struct Stash {
     Sym<QT> r;
-    Flow<QT> fl;
+    Flow<QT, DIM> fl;
     Sym<QT> q;
   };
   auto qp_of = [](const Stash& st) {
@@ -422,8 +431,8 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
       else
         G[a][2] = QT(0);
     }
-    st.fl = flow_terms<QT, true>(u, G, cq);
-    st.r = be_rate_flow<QT, true>(q, H, d, st.fl, cq);
+    st.fl = flow_terms<QT, true, DIM>(u, G, cq);
+    st.r = be_rate_flow<QT, true, DIM>(q, H, d, st.fl, cq);
     st.q = q;
     return qp_of(st);
   };
@@ -453,7 +462,7 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
       Sym<QT> pcc, Lp, d[3];
       stencil_lds_iso2<QT, R1::W, R1::N, false>(sP[ps], k1, pcc, d, Lp);
       const Sym<QT> H = SR ? molecular_field_exact(pcc, Lp, cq) : molecular_field(pcc, Lp, cq);
-      const Sym<QT> Rp = be_rate_flow<QT, true>(pcc, H, d, st.fl, cq);
+      const Sym<QT> Rp = be_rate_flow<QT, true, DIM>(pcc, H, d, st.fl, cq);
       const uint32_t s = uint32_t(x0 + tx) + uint32_t(g.nx) * (uint32_t(y0 + ty) + uint32_t(g.ny) * uint32_t(z));
       store_q_update<QT, SR>(Qout, N, int64_t(s), st.q, st.r, Rp, srkey);
       return;
@@ -483,17 +492,21 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
                           Sym<QT>{dz[0], dz[1], dz[2], dz[3], dz[4]}};
     const Sym<QT> Lp{lap[0], lap[1], lap[2], lap[3], lap[4]};
     const Sym<QT> H = SR ? molecular_field_exact(pc, Lp, cq) : molecular_field(pc, Lp, cq);
-    const Sym<QT> Rp = be_rate_flow<QT, true>(pc, H, d, st.fl, cq);
+    const Sym<QT> Rp = be_rate_flow<QT, true, DIM>(pc, H, d, st.fl, cq);
     const uint32_t s = uint32_t(x0 + tx) + uint32_t(g.nx) * (uint32_t(y0 + ty) + uint32_t(g.ny) * uint32_t(z));
     store_q_update<QT, SR>(Qout, N, int64_t(s), st.q, st.r, Rp, srkey);
   };
 
   if constexpr (DIM == 2) {
-    load_q(0, 0);
+    QRegs qr;
+    FRegs fr;
+    fetch_q(0, qr);
+    fetch_f(0, fr);
+    store_q(0, qr);
     __syncthreads();
     stress_plane(0, 0, 0, 0, 0);
     __syncthreads();
-    lb_plane(0, 0, 0, 0, 0, true, nullptr);
+    lb_plane(0, 0, 0, 0, 0, true, &fr);
     __syncthreads();
     Stash st;
     pred_plane(0, 0, 0, 0, 0, 0, 0, st);

@@ -197,26 +197,40 @@ struct RegionSrc {
   __device__ __forceinline__ A operator()(int q, uint32_t s) const { return q < NA ? a[q][s] : A(b[q - NA][s]); }
 };
 
-// Load plane gz of NC component arrays (component stride N) into an LDS
-// plane over the R2 region of the block, with periodic wrap.
-// dst points at an LDS plane laid out [NC][R2].
-template <typename S, int TX, int TY, int NC, typename SRC>
-__device__ __forceinline__ void load_region(S* dst, const SRC& src, int x0, int y0, int gz, const GridDims& g,
-                                            int tid) {
-  constexpr int W2 = TX + 4, R2 = (TX + 4) * (TY + 4), NT = TX * TY;
-  const uint32_t plane = uint32_t(g.nx) * uint32_t(g.ny) * uint32_t(gz);
-  for (int k = tid; k < R2; k += NT) {
-    const int i = k % W2, j = k / W2;
-    const int gx = wrapi(x0 - 2 + i, g.nx), gy = wrapi(y0 - 2 + j, g.ny);
-    const uint32_t s = plane + uint32_t(gx) + uint32_t(g.nx) * uint32_t(gy);
-#pragma unroll
-    for (int q = 0; q < NC; q++) dst[q * R2 + k] = src(q, s);
-  }
-}
+// v modulo n for -n <= v < 2n, without a division.
+__device__ __forceinline__ int wrap_near(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 
-// Register-staged form of load_region for software pipelining: fetch_region
-// issues the global loads of a plane into registers (one iteration ahead),
-// store_region later writes them to an LDS plane.
+// The R2 region of a block, one point per thread and pass: the in-plane
+// (periodic) site index of each of the thread's points, formed once per
+// block.  Tiles at least as wide as the grid may wrap more than once and
+// take the division; all others do without (a runtime division costs some
+// 20 instructions, and there are two per point).
+template <int TX, int TY>
+struct RegionIdx {
+  static constexpr int W2 = TX + 4, R2 = (TX + 4) * (TY + 4), NT = TX * TY;
+  static constexpr int P = (R2 + NT - 1) / NT;  // points per thread
+  uint32_t off[P];
+  __device__ __forceinline__ RegionIdx(int x0, int y0, const GridDims& g, int tid) {
+    if (g.nx >= TX + 4 && g.ny >= TY + 4) {
+#pragma unroll
+      for (int p = 0; p < P; p++) {
+        const int k = tid + p * NT;
+        off[p] = uint32_t(wrap_near(x0 - 2 + k % W2, g.nx)) + uint32_t(g.nx) * uint32_t(wrap_near(y0 - 2 + k / W2, g.ny));
+      }
+    } else {
+#pragma unroll
+      for (int p = 0; p < P; p++) {
+        const int k = tid + p * NT;
+        off[p] = uint32_t(wrapi(x0 - 2 + k % W2, g.nx)) + uint32_t(g.nx) * uint32_t(wrapi(y0 - 2 + k / W2, g.ny));
+      }
+    }
+  }
+};
+
+// Plane gz of NC component arrays (component stride N) over the R2 region of
+// the block, with periodic wrap: fetch_region issues the global loads into
+// registers, store_region later writes them to an LDS plane laid out
+// [NC][R2].  Every load is in flight before the first value is stored.
 template <typename S, int TX, int TY, int NC>
 struct RegionRegs {
   static constexpr int R2 = (TX + 4) * (TY + 4), NT = TX * TY;
@@ -225,18 +239,15 @@ struct RegionRegs {
 };
 
 template <typename S, int TX, int TY, int NC, typename SRC>
-__device__ __forceinline__ void fetch_region(RegionRegs<S, TX, TY, NC>& r, const SRC& src, int x0, int y0, int gz,
-                                             const GridDims& g, int tid) {
+__device__ __forceinline__ void fetch_region(RegionRegs<S, TX, TY, NC>& r, const SRC& src,
+                                             const RegionIdx<TX, TY>& idx, int gz, const GridDims& g, int tid) {
   using RR = RegionRegs<S, TX, TY, NC>;
-  constexpr int W2 = TX + 4;
   const uint32_t plane = uint32_t(g.nx) * uint32_t(g.ny) * uint32_t(gz);
 #pragma unroll
   for (int p = 0; p < RR::P; p++) {
     const int k = tid + p * RR::NT;
     if (p < RR::P - 1 || k < RR::R2) {
-      const int i = k % W2, j = k / W2;
-      const int gx = wrapi(x0 - 2 + i, g.nx), gy = wrapi(y0 - 2 + j, g.ny);
-      const uint32_t s = plane + uint32_t(gx) + uint32_t(g.nx) * uint32_t(gy);
+      const uint32_t s = plane + idx.off[p];
 #pragma unroll
       for (int q = 0; q < NC; q++) r.v[p][q] = src(q, s);
     }
@@ -518,12 +529,15 @@ __device__ __forceinline__ void split_lb_body(const QT* __restrict__ Qin, const 
     for (int i = 0; i < L::q; i++) store_out(&(fout + size_t(i) * size_t(N))[s], f[i]);
   };
 
+  const RegionIdx<TX, TY> ridx(x0, y0, g, tid);
   if constexpr (DIM == 2) {
-    load_region<QT, TX, TY, 5>(&sQ[0][0][0], qsrc, x0, y0, 0, g, tid);
-    __syncthreads();
+    RegionRegs<QT, TX, TY, 5> rq;
+    fetch_region<QT, TX, TY, 5>(rq, qsrc, ridx, 0, g, tid);
     QT tz[3];
     S f[L::q];
     fetch_f(0, f);
+    store_region<QT, TX, TY, 5>(rq, &sQ[0][0][0], tid);
+    __syncthreads();
     tau_plane(0, 0, 0, 0, tz);
     __syncthreads();
     lb_site(0, 0, tz, tz, f);
@@ -534,14 +548,19 @@ __device__ __forceinline__ void split_lb_body(const QT* __restrict__ Qin, const 
     // software pipeline: the halo region of plane p+2 and the populations of
     // plane p are in flight while plane p's stress and plane p-1's update run
     RegionRegs<QT, TX, TY, 5> rq;
-    load_region<QT, TX, TY, 5>(&sQ[slot(zb - 2)][0][0], qsrc, x0, y0, wrapi(zb - 2, g.nz), g, tid);
-    load_region<QT, TX, TY, 5>(&sQ[slot(zb - 1)][0][0], qsrc, x0, y0, wrapi(zb - 1, g.nz), g, tid);
-    fetch_region<QT, TX, TY, 5>(rq, qsrc, x0, y0, wrapi(zb, g.nz), g, tid);
+    {
+      RegionRegs<QT, TX, TY, 5> ra, rb;
+      fetch_region<QT, TX, TY, 5>(ra, qsrc, ridx, wrapi(zb - 2, g.nz), g, tid);
+      fetch_region<QT, TX, TY, 5>(rb, qsrc, ridx, wrapi(zb - 1, g.nz), g, tid);
+      fetch_region<QT, TX, TY, 5>(rq, qsrc, ridx, wrapi(zb, g.nz), g, tid);
+      store_region<QT, TX, TY, 5>(ra, &sQ[slot(zb - 2)][0][0], tid);
+      store_region<QT, TX, TY, 5>(rb, &sQ[slot(zb - 1)][0][0], tid);
+    }
     QT tzA[3] = {QT(0), QT(0), QT(0)}, tzB[3] = {QT(0), QT(0), QT(0)}, tzC[3];
     S f[L::q];
     for (int p = zb - 1; p <= ze; p++) {
       store_region<QT, TX, TY, 5>(rq, &sQ[slot(p + 1)][0][0], tid);
-      if (p + 2 <= ze + 1) fetch_region<QT, TX, TY, 5>(rq, qsrc, x0, y0, wrapi(p + 2, g.nz), g, tid);
+      if (p + 2 <= ze + 1) fetch_region<QT, TX, TY, 5>(rq, qsrc, ridx, wrapi(p + 2, g.nz), g, tid);
       __syncthreads();
       tau_plane(slot(p), slot(p + 1), slot(p - 1), p & 1, tzC);
       __syncthreads();
@@ -616,7 +635,7 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
   // expression, so the same rounding as the value shared through LDS).
   struct Stash {
     Sym<S> r;
-    Flow<S> fl;
+    Flow<S, DIM> fl;
     Sym<S> q;
   };
   auto qp_of = [](const Stash& st) {
@@ -667,8 +686,8 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
       else
         G[a][2] = S(0);
     }
-    st.fl = flow_terms<S, true>(u, G, c);
-    st.r = be_rate_flow<S, true>(q, H, d, st.fl, c);
+    st.fl = flow_terms<S, true, DIM>(u, G, c);
+    st.r = be_rate_flow<S, true, DIM>(q, H, d, st.fl, c);
     st.q = q;
     return qp_of(st);
   };
@@ -696,7 +715,7 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
       else
         stencil_lds_iso3<S, T::W1, T::R1, false>(sP[b], sP[bzp], sP[bzm], k1, pcc, d, Lp);
       const Sym<S> H = SR ? molecular_field_exact(pcc, Lp, c) : molecular_field(pcc, Lp, c);
-      const Sym<S> Rp = be_rate_flow<S, true>(pcc, H, d, st.fl, c);
+      const Sym<S> Rp = be_rate_flow<S, true, DIM>(pcc, H, d, st.fl, c);
       const int64_t s = x + (int64_t)g.nx * (y + (int64_t)g.ny * z);
       if (rec) store_sym(rec, N, s, pcc);
       store_q_update<S, SR>(Qout, N, s, st.q, st.r, Rp, srkey);
@@ -727,14 +746,17 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
                          Sym<S>{dz[0], dz[1], dz[2], dz[3], dz[4]}};
     const Sym<S> Lp{lap[0], lap[1], lap[2], lap[3], lap[4]};
     const Sym<S> H = SR ? molecular_field_exact(pc, Lp, c) : molecular_field(pc, Lp, c);
-    const Sym<S> Rp = be_rate_flow<S, true>(pc, H, d, st.fl, c);
+    const Sym<S> Rp = be_rate_flow<S, true, DIM>(pc, H, d, st.fl, c);
     const int64_t s = x + (int64_t)g.nx * (y + (int64_t)g.ny * z);
     if (rec) store_sym(rec, N, s, pc);  // record the predictor (reverse-mode replay)
     store_q_update<S, SR>(Qout, N, s, st.q, st.r, Rp, srkey);
   };
 
+  const RegionIdx<TX, TY> ridx(x0, y0, g, tid);
   if constexpr (DIM == 2) {
-    load_region<S, TX, TY, NC>(&sQ[0][0][0], csrc, x0, y0, 0, g, tid);
+    RegionRegs<S, TX, TY, NC> rq;
+    fetch_region<S, TX, TY, NC>(rq, csrc, ridx, 0, g, tid);
+    store_region<S, TX, TY, NC>(rq, &sQ[0][0][0], tid);
     __syncthreads();
     Stash st;
     const Sym<S> pc = pred_point(0, 0, 0, tx + 1, ty + 1, st);
@@ -752,9 +774,14 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
     const int ze = min(zb + zc, g.nz);
     auto slot = [](int p) { return (p + 3) % 3; };  // p >= -3
     RegionRegs<S, TX, TY, NC> rq;
-    load_region<S, TX, TY, NC>(&sQ[slot(zb - 2)][0][0], csrc, x0, y0, wrapi(zb - 2, g.nz), g, tid);
-    load_region<S, TX, TY, NC>(&sQ[slot(zb - 1)][0][0], csrc, x0, y0, wrapi(zb - 1, g.nz), g, tid);
-    fetch_region<S, TX, TY, NC>(rq, csrc, x0, y0, wrapi(zb, g.nz), g, tid);
+    {
+      RegionRegs<S, TX, TY, NC> ra, rb;
+      fetch_region<S, TX, TY, NC>(ra, csrc, ridx, wrapi(zb - 2, g.nz), g, tid);
+      fetch_region<S, TX, TY, NC>(rb, csrc, ridx, wrapi(zb - 1, g.nz), g, tid);
+      fetch_region<S, TX, TY, NC>(rq, csrc, ridx, wrapi(zb, g.nz), g, tid);
+      store_region<S, TX, TY, NC>(ra, &sQ[slot(zb - 2)][0][0], tid);
+      store_region<S, TX, TY, NC>(rb, &sQ[slot(zb - 1)][0][0], tid);
+    }
     auto pslot = [](int p) { return (p + 3) % 3; };  // p >= -3
     Sym<S> pm = sym_zero<S>();  // Q^P of plane p-2 at the owner's site (ZREG)
     // one plane of the pipeline: predictor of plane p, corrector of p-1;
@@ -763,7 +790,7 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
       // slot(p+1) = slot(p-2) was last read by the predictor of iteration
       // p-1, before that iteration's second barrier
       store_region<S, TX, TY, NC>(rq, &sQ[slot(p + 1)][0][0], tid);
-      if (p + 2 <= ze + 1) fetch_region<S, TX, TY, NC>(rq, csrc, x0, y0, wrapi(p + 2, g.nz), g, tid);
+      if (p + 2 <= ze + 1) fetch_region<S, TX, TY, NC>(rq, csrc, ridx, wrapi(p + 2, g.nz), g, tid);
       // plane p+1 of Q and u, and the Q^P written in iteration p-1, are
       // visible after this barrier
       __syncthreads();

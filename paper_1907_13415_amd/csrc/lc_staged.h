@@ -208,6 +208,32 @@ __device__ __forceinline__ void moments(const S (&f)[Lattice<LAT>::q], const S (
   moments<LAT, S, DEV>(f, F, rho, u, mass);
 }
 
+// c_i . v and the dot product of two vectors of the lattice's dimension,
+// without the products by zero velocity components (the compiler must keep
+// 0 * v, which is not zero for every v; exact sums either way).
+template <int LAT, typename S>
+__device__ __forceinline__ S lat_dot(int i, const S (&v)[3]) {
+  S r = S(0);
+  bool some = false;
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    const int ca = lat_c<LAT>(i, a);
+    if (ca == 0) continue;
+    const S t = ca > 0 ? v[a] : -v[a];
+    r = some ? r + t : t;
+    some = true;
+  }
+  return r;
+}
+
+template <int LAT, typename S>
+__device__ __forceinline__ S dim_dot(const S (&a)[3], const S (&b)[3]) {
+  if constexpr (Lattice<LAT>::dim == 3)
+    return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
+  else
+    return a[0] * b[0] + a[1] * b[1];
+}
+
 // BGK collision with the forcing term of Sec. 1.2.1, in place on f.
 // Equilibrium Eq. (8) with c_s^2 = 1/3; in DEV form the rest weight w_i is
 // removed from both f and f_eq, so only deviations are formed.
@@ -217,14 +243,14 @@ template <int LAT, typename S, bool DEV>
 __device__ __forceinline__ void collide(S (&f)[Lattice<LAT>::q], S rho, S mass, const S (&u)[3], const S (&F)[3],
                                         const Coef<S>& c) {
   using L = Lattice<LAT>;
-  const S uu15 = S(1.5) * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
-  const S uF3 = S(3) * (u[0] * F[0] + u[1] * F[1] + u[2] * F[2]);
+  const S uu15 = S(1.5) * dim_dot<LAT>(u, u);
+  const S uF3 = S(3) * dim_dot<LAT>(u, F);
   const S drho = mass;
 #pragma unroll
   for (int i = 0; i < L::q; i++) {
     const S w = S(L::w(i));
-    const S cu = S(L::cx(i)) * u[0] + S(L::cy(i)) * u[1] + S(L::cz(i)) * u[2];
-    const S cF = S(L::cx(i)) * F[0] + S(L::cy(i)) * F[1] + S(L::cz(i)) * F[2];
+    const S cu = lat_dot<LAT>(i, u);
+    const S cF = lat_dot<LAT>(i, F);
     // f_eq - (DEV ? w : 0)
     const S feq = DEV ? w * (drho + rho * (S(3) * cu + S(4.5) * cu * cu - uu15))
                       : w * rho * (S(1) + S(3) * cu + S(4.5) * cu * cu - uu15);
@@ -240,8 +266,8 @@ template <int LAT, typename S, bool DEV>
 __device__ __forceinline__ void collide_pairs(S (&f)[Lattice<LAT>::q], S rho, S mass, const S (&u)[3],
                                               const S (&F)[3], const Coef<S>& c) {
   using L = Lattice<LAT>;
-  const S uu15 = S(1.5) * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
-  const S uF3 = S(3) * (u[0] * F[0] + u[1] * F[1] + u[2] * F[2]);
+  const S uu15 = S(1.5) * dim_dot<LAT>(u, u);
+  const S uF3 = S(3) * dim_dot<LAT>(u, F);
   const S base = mass;
   const S keep = S(1) - c.omega;
   const S om_rho = c.omega * rho;
@@ -256,8 +282,8 @@ __device__ __forceinline__ void collide_pairs(S (&f)[Lattice<LAT>::q], S rho, S 
     if (L::opp(i) < i) continue;
     const int j = L::opp(i);
     const S w = S(L::w(i));
-    const S cu = S(L::cx(i)) * u[0] + S(L::cy(i)) * u[1] + S(L::cz(i)) * u[2];
-    const S cF = S(L::cx(i)) * F[0] + S(L::cy(i)) * F[1] + S(L::cz(i)) * F[2];
+    const S cu = lat_dot<LAT>(i, u);
+    const S cF = lat_dot<LAT>(i, F);
     const S even = w * (c.omega * base + om_rho * (S(4.5) * cu * cu - uu15) + c.src * (S(9) * cF * cu - uF3));
     const S odd = w * S(3) * (om_rho * cu + c.src * cF);
     const S fi = f[i], fj = f[j];
@@ -280,8 +306,8 @@ __device__ __forceinline__ void collide_mrt(S (&f)[Lattice<LAT>::q], S rho, S ma
                                             const S (&F)[3], const Coef<S>& c) {
   using L = Lattice<LAT>;
   using Gh = Ghosts<LAT>;
-  const S uu15 = S(1.5) * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
-  const S uF3 = S(3) * (u[0] * F[0] + u[1] * F[1] + u[2] * F[2]);
+  const S uu15 = S(1.5) * dim_dot<LAT>(u, u);
+  const S uF3 = S(3) * dim_dot<LAT>(u, F);
   const S base = mass;
   S hs[L::q], hd[L::q];  // per pair representative i: h_i + h_-i, h_i - h_-i; hs[0] = h_0
   {
@@ -296,8 +322,8 @@ __device__ __forceinline__ void collide_mrt(S (&f)[Lattice<LAT>::q], S rho, S ma
     if (L::opp(i) < i) continue;
     const int j = L::opp(i);
     const S w = S(L::w(i));
-    const S cu = S(L::cx(i)) * u[0] + S(L::cy(i)) * u[1] + S(L::cz(i)) * u[2];
-    const S cF = S(L::cx(i)) * F[0] + S(L::cy(i)) * F[1] + S(L::cz(i)) * F[2];
+    const S cu = lat_dot<LAT>(i, u);
+    const S cF = lat_dot<LAT>(i, F);
     const S eq_e = w * (base + rho * (S(4.5) * cu * cu - uu15));
     const S eq_o = w * S(3) * rho * cu;
     const S g_e = w * (S(9) * cF * cu - uF3);
