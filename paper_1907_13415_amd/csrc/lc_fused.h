@@ -25,7 +25,7 @@
 //       store of the post-collision populations (pull form);
 //   (d) predictor of plane p-3 on the radius-1 rectangle;
 //   (e) corrector of plane p-4 at the tile's sites, store of Q(n+1).
-// Region loops visit the tile's own sites first, in thread order, so the
+// (On two-dimensional grids: lc_fused2d.h.)  Region loops visit the tile's own sites first, in thread order, so the
 // thread that computes a site's predictor also computes its corrector from
 // values it keeps in registers, and the tile's collisions store whole rows.
 #pragma once
@@ -69,50 +69,26 @@ __device__ __forceinline__ void tile_first(int k, int& i, int& j) {
   i = c < r ? c : TX + c;
 }
 
-// Tile shapes of the single pass (LDS per block: FP32 D3Q19 about 132 KB,
-// FP64 D3Q19 about 152 KB, so one block per CU in 3D) and threads per block
-// (more threads than tile sites share the ring work and hide latency).
-// On two-dimensional grids the runtime picks one of the FUSED2D_* shapes
-// from the number of tiles.
-template <int LAT, typename QT>
+// Tile shapes of the single pass in 3D (LDS per block: FP32 about 132 KB,
+// FP64 about 152 KB, so one block per CU) and threads per block (more
+// threads than tile sites share the ring work and hide latency).
+template <typename QT>
 struct FusedCfg {
-  static constexpr bool d3 = Lattice<LAT>::dim == 3;
   static constexpr bool f64 = sizeof(QT) == 8;
-  static constexpr int TX = (d3 && f64) ? 16 : 32, TY = 8;
-  static constexpr int NTHR = d3 ? (f64 ? 256 : 512) : TX * TY;
+  static constexpr int TX = f64 ? 16 : 32, TY = 8;
+  static constexpr int NTHR = f64 ? 256 : 512;
   static constexpr int ZC = 64;  // planes per block along z
 };
 
-// Two-dimensional shapes (TX, TY, threads).  A grid of at most one tile per
-// CU is latency bound (one wave per SIMD with one thread per site): there a
-// block of 1024 threads shares each stage's ring points among four threads
-// per tile site, which shortens every wave's instruction stream and puts
-// four waves on each SIMD; 16x8 tiles where the grid has few enough of
-// them, else 32x8.  Up to four tiles per CU, two threads per site; larger
-// grids keep one thread per site.  Measured on 65536 sites (256^2): 8.3 ->
-// 6.1 us per step in FP32, 9.2 -> 7.3 us in FP64; on 16384 sites (128^2)
-// 16x8 tiles 5.3 us (FP32) against 5.7 for 32x8 at 1024 threads; on 384^2
-// two threads per site 9.5 against 10.8 us (FP32), 14.6 against 18.2 us
-// (FP64).
-constexpr int FUSED2D_SMALL_TX = 16, FUSED2D_SMALL_TY = 8, FUSED2D_SMALL_NTHR = 1024;
-constexpr int FUSED2D_MID_TX = 32, FUSED2D_MID_TY = 8, FUSED2D_MID_NTHR = 1024;
-constexpr int FUSED2D_HALF_TX = 32, FUSED2D_HALF_TY = 8, FUSED2D_HALF_NTHR = 512;
-constexpr int FUSED2D_WIDE_TX = 32, FUSED2D_WIDE_TY = 8, FUSED2D_WIDE_NTHR = 256;
-constexpr int FUSED2D_CUS = 256;  // compute units of the chip
-
-// ST: the difference stencils (lc_staged.h); the isotropic ones on
-// two-dimensional grids only, with the arithmetic of the two sweeps (the
-// whole stress of the radius-3 rectangle, corners included, in LDS for the
-// body force; the stencils of Q, u and Q^P from the pairs of opposite
-// velocities).
-template <int LAT, typename S, bool DEV, int TX, int TY, int NTHR, bool MRT, typename QT, bool SR,
-          int ST = STENCIL_COMPACT>
+// The single pass in three dimensions (compact stencils).
+template <typename S, bool DEV, int TX, int TY, int NTHR, bool MRT, typename QT, bool SR>
 __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* __restrict__ fin,
                                            S* __restrict__ fout, QT* __restrict__ Qout, const GridDims& g,
                                            const Coef<S>& c, const Coef<QT>& cq, int zc, int bx, int by, int bz,
                                            uint32_t srkey) {
+  constexpr int LAT = 1;
   using L = Lattice<LAT>;
-  constexpr int DIM = L::dim;
+  constexpr int DIM = 3;
   constexpr int NT = TX * TY;
   using R4 = Rect<TX, TY, 4>;
   using R3 = Rect<TX, TY, 3>;
@@ -122,19 +98,16 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
   // radius 2 (for d_x at the radius-2 sites), tau_{a y} the other way round
   constexpr int WX = R3::W, NXA = R3::W * R2::H;
   constexpr int WY = R2::W, NYA = R2::W * R3::H;
-  constexpr int NQS = DIM == 3 ? 5 : 1;  // Q planes p-4 .. p
-  constexpr int NTS = DIM == 3 ? 2 : 1;  // in-plane stress planes
-  constexpr int NZS = DIM == 3 ? 3 : 1;  // tau_{a z} planes
-  constexpr int NUS = DIM == 3 ? 3 : 1;  // velocity planes
-  constexpr int NPS = DIM == 3 ? 2 : 1;  // predictor planes
-  constexpr bool ISO = ST == STENCIL_ISO;
-  static_assert(!ISO || DIM == 2, "isotropic stencils in the single pass: two-dimensional grids");
+  constexpr int NQS = 5;  // Q planes p-4 .. p
+  constexpr int NTS = 2;  // in-plane stress planes
+  constexpr int NZS = 3;  // tau_{a z} planes
+  constexpr int NUS = 3;  // velocity planes
+  constexpr int NPS = 2;  // predictor planes
   __shared__ QT sQ[NQS][5][R4::N];
-  __shared__ QT sTx[NTS][DIM][ISO ? 1 : NXA];
-  __shared__ QT sTy[NTS][DIM][ISO ? 1 : NYA];
-  __shared__ QT sTi[ISO ? 2 : 1][ISO ? 2 : 1][ISO ? R3::N : 1];  // isotropic: tau_ab on the radius-3 rectangle
-  __shared__ QT sTz[NZS][DIM == 3 ? 3 : 1][DIM == 3 ? R2::N : 1];
-  __shared__ QT sU[NUS][DIM][R2::N];
+  __shared__ QT sTx[NTS][3][NXA];
+  __shared__ QT sTy[NTS][3][NYA];
+  __shared__ QT sTz[NZS][3][R2::N];
+  __shared__ QT sU[NUS][3][R2::N];
   __shared__ QT sP[NPS][5][R1::N];
 
   static_assert(NTHR >= NT, "one thread per tile site at least");
@@ -181,12 +154,10 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
   else
     in_plane([](int v, int n) { return wrapi(v, n); });
 
-  // Register staging of the global loads: in 3D (float forms, where registers
-  // allow) the Q rectangle of plane p+1 and the populations of the next
-  // moment plane are in flight while the stages of plane p run; in 2D every
-  // load of the block is issued before the first stage, so a step waits for
-  // memory once and not once per stage that reads it.
-  constexpr bool PF = DIM == 2 || sizeof(QT) == 4;
+  // Register staging of the next plane's global loads (float forms, where
+  // registers allow): the Q rectangle of plane p+1 and the populations of the
+  // next moment plane are in flight while the stages of plane p run.
+  constexpr bool PF = sizeof(QT) == 4;
   struct QRegs {
     QT v[PF ? P4 : 1][5];
   };
@@ -234,21 +205,6 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
   // (b) stress of the plane in slot m (z neighbours in zp, zm) on the
   // radius-3 rectangle without its corners
   auto stress_plane = [&](int m, int zp, int zm, int ts, int zs) {
-    if constexpr (ISO) {  // every point of the rectangle: the body force reads the diagonal neighbours
-      for (int k = tid; k < R3::N; k += NTHR) {
-        const int i3 = k % R3::W, j3 = k / R3::W;
-        Sym<QT> q, Lq, d[3];
-        stencil_lds_iso2<QT, R4::W, R4::N>(sQ[m], (i3 + 1) + R4::W * (j3 + 1), q, d, Lq);
-        const Sym<QT> H = molecular_field(q, Lq, cq);
-        QT t[3][3];
-        stress(q, H, d, cq, t);
-#pragma unroll
-        for (int a = 0; a < 2; a++)
-#pragma unroll
-          for (int b = 0; b < 2; b++) sTi[a][b][k] = t[a][b];
-      }
-      return;
-    }
     for (int k = tid; k < R3::N; k += NTHR) {
       const int i3 = k % R3::W, j3 = k / R3::W;
       const bool xin = i3 >= 1 && i3 < R3::W - 1, yin = j3 >= 1 && j3 < R3::H - 1;
@@ -268,12 +224,10 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
 #pragma unroll
         for (int a = 0; a < DIM; a++) sTy[ts][a][ky] = t[a][1];
       }
-      if constexpr (DIM == 3) {
-        if (xin && yin) {
-          const int k2 = (i3 - 1) + R2::W * (j3 - 1);
+      if (xin && yin) {
+        const int k2 = (i3 - 1) + R2::W * (j3 - 1);
 #pragma unroll
-          for (int a = 0; a < 3; a++) sTz[zs][a][k2] = t[a][2];
-        }
+        for (int a = 0; a < 3; a++) sTz[zs][a][k2] = t[a][2];
       }
     }
   };
@@ -328,35 +282,12 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
       tile_first<TX, TY, 2>(k, i2, j2);
       const int k2 = i2 + R2::W * j2;
       S F[3] = {S(0), S(0), S(0)};
-      if constexpr (ISO) {  // F_a = 3 sum_i w_i sum_b c_ib tau_ab(x + c_i), over pairs
-        const int k3 = (i2 + 1) + R3::W * (j2 + 1);
 #pragma unroll
-        for (int a = 0; a < DIM; a++) {
-          QT acc = QT(0);
-#pragma unroll
-          for (int i = 1; i < L::q; i++) {
-            if (L::opp(i) < i) continue;
-            const int o = L::cx(i) + R3::W * L::cy(i);
-            QT dsum = QT(0);
-#pragma unroll
-            for (int b = 0; b < DIM; b++) {
-              const int cb = b == 0 ? L::cx(i) : L::cy(i);
-              if (cb == 0) continue;
-              const QT dt = sTi[a][b][k3 + o] - sTi[a][b][k3 - o];
-              dsum += cb > 0 ? dt : -dt;
-            }
-            acc += QT(3.0 * L::w(i)) * dsum;
-          }
-          F[a] = S(acc);
-        }
-      } else {
-#pragma unroll
-        for (int a = 0; a < DIM; a++) {
-          const int kx = (i2 + 1) + WX * j2, ky = i2 + WY * (j2 + 1);
-          QT acc = (sTx[ts][a][kx + 1] - sTx[ts][a][kx - 1]) + (sTy[ts][a][ky + WY] - sTy[ts][a][ky - WY]);
-          if constexpr (DIM == 3) acc += sTz[zsp][a][k2] - sTz[zsm][a][k2];
-          F[a] = S(QT(0.5) * acc);
-        }
+      for (int a = 0; a < DIM; a++) {
+        const int kx = (i2 + 1) + WX * j2, ky = i2 + WY * (j2 + 1);
+        QT acc = (sTx[ts][a][kx + 1] - sTx[ts][a][kx - 1]) + (sTy[ts][a][ky + WY] - sTy[ts][a][ky - WY]);
+        acc += sTz[zsp][a][k2] - sTz[zsm][a][k2];
+        F[a] = S(QT(0.5) * acc);
       }
       const uint32_t site = plane + ip[n].s;
       S f[L::q];
@@ -397,39 +328,15 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
     const int k4 = (i1 + 3) + R4::W * (j1 + 3);
     const int k2 = (i1 + 1) + R2::W * (j1 + 1);
     Sym<QT> q, Lq, d[3];
-    if constexpr (ISO)
-      stencil_lds_iso2<QT, R4::W, R4::N, false>(sQ[m], k4, q, d, Lq);
-    else
-      stencil_lds<QT, DIM, R4::W, R4::N, false>(sQ[m], sQ[zp], sQ[zm], k4, q, d, Lq);
+    stencil_lds<QT, DIM, R4::W, R4::N, false>(sQ[m], sQ[zp], sQ[zm], k4, q, d, Lq);
     const Sym<QT> H = SR ? molecular_field_exact(q, Lq, cq) : molecular_field(q, Lq, cq);
     QT u[3], G[3][3];
 #pragma unroll
     for (int a = 0; a < 3; a++) {
-      u[a] = a < DIM ? sU[um][a][k2] * QT(0.5) : QT(0);
-      if constexpr (ISO) {  // undivided: 6 sum_i w_i c_ib u_a(x + c_i), over pairs
-        QT g0 = QT(0), g1 = QT(0), g2 = QT(0);
-        if (a < DIM) {
-#pragma unroll
-          for (int i = 1; i < L::q; i++) {
-            if (L::opp(i) < i) continue;
-            const int o = L::cx(i) + R2::W * L::cy(i);
-            const QT dif = sU[um][a][k2 + o] - sU[um][a][k2 - o];
-            const QT w6 = QT(6.0 * L::w(i));
-            if (L::cx(i) != 0) g0 += (L::cx(i) > 0 ? w6 : -w6) * dif;
-            if (L::cy(i) != 0) g1 += (L::cy(i) > 0 ? w6 : -w6) * dif;
-          }
-        }
-        G[a][0] = g0;
-        G[a][1] = g1;
-        G[a][2] = g2;
-        continue;
-      }
-      G[a][0] = a < DIM ? sU[um][a][k2 + 1] - sU[um][a][k2 - 1] : QT(0);
-      G[a][1] = a < DIM ? sU[um][a][k2 + R2::W] - sU[um][a][k2 - R2::W] : QT(0);
-      if constexpr (DIM == 3)
-        G[a][2] = sU[uzp][a][k2] - sU[uzm][a][k2];
-      else
-        G[a][2] = QT(0);
+      u[a] = sU[um][a][k2] * QT(0.5);
+      G[a][0] = sU[um][a][k2 + 1] - sU[um][a][k2 - 1];
+      G[a][1] = sU[um][a][k2 + R2::W] - sU[um][a][k2 - R2::W];
+      G[a][2] = sU[uzp][a][k2] - sU[uzm][a][k2];
     }
     st.fl = flow_terms<QT, true, DIM>(u, G, cq);
     st.r = be_rate_flow<QT, true, DIM>(q, H, d, st.fl, cq);
@@ -458,15 +365,6 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
   const int k1 = (tx + 1) + R1::W * (ty + 1);
   auto corr_site = [&](int z, int ps, const Stash& st, const Sym<QT>& pc, const Sym<QT>& pzp, const Sym<QT>& pzm) {
     if (!own) return;
-    if constexpr (ISO) {
-      Sym<QT> pcc, Lp, d[3];
-      stencil_lds_iso2<QT, R1::W, R1::N, false>(sP[ps], k1, pcc, d, Lp);
-      const Sym<QT> H = SR ? molecular_field_exact(pcc, Lp, cq) : molecular_field(pcc, Lp, cq);
-      const Sym<QT> Rp = be_rate_flow<QT, true, DIM>(pcc, H, d, st.fl, cq);
-      const uint32_t s = uint32_t(x0 + tx) + uint32_t(g.nx) * (uint32_t(y0 + ty) + uint32_t(g.ny) * uint32_t(z));
-      store_q_update<QT, SR>(Qout, N, int64_t(s), st.q, st.r, Rp, srkey);
-      return;
-    }
     const QT vc[5] = {pc.xx, pc.xy, pc.xz, pc.yy, pc.yz};
     const QT vzp[5] = {pzp.xx, pzp.xy, pzp.xz, pzp.yy, pzp.yz};
     const QT vzm[5] = {pzm.xx, pzm.xy, pzm.xz, pzm.yy, pzm.yz};
@@ -479,14 +377,9 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
       dx[q] = xp - xm;
       dy[q] = yp - ym;
       QT l = (xp + xm) + (yp + ym);
-      if constexpr (DIM == 3) {
-        dz[q] = vzp[q] - vzm[q];
-        l += vzp[q] + vzm[q];
-        lap[q] = l - QT(6) * cc;
-      } else {
-        dz[q] = QT(0);
-        lap[q] = l - QT(4) * cc;
-      }
+      dz[q] = vzp[q] - vzm[q];
+      l += vzp[q] + vzm[q];
+      lap[q] = l - QT(6) * cc;
     }
     const Sym<QT> d[3] = {Sym<QT>{dx[0], dx[1], dx[2], dx[3], dx[4]}, Sym<QT>{dy[0], dy[1], dy[2], dy[3], dy[4]},
                           Sym<QT>{dz[0], dz[1], dz[2], dz[3], dz[4]}};
@@ -497,78 +390,59 @@ __device__ __forceinline__ void fused_body(const QT* __restrict__ Qin, const S* 
     store_q_update<QT, SR>(Qout, N, int64_t(s), st.q, st.r, Rp, srkey);
   };
 
-  if constexpr (DIM == 2) {
-    QRegs qr;
-    FRegs fr;
-    fetch_q(0, qr);
-    fetch_f(0, fr);
-    store_q(0, qr);
+  const int zb = bz * zc;
+  const int ze = min(zb + zc, g.nz);
+  // ring slots of plane p (p >= zb - 8 > -2^30)
+  auto s5 = [](int p) { return (p + (1 << 30)) % 5; };
+  auto s3 = [](int p) { return (p + (1 << 30)) % 3; };
+  auto s2 = [](int p) { return (p + (1 << 30)) & 1; };
+  Sym<QT> pm = sym_zero<QT>();  // Q^P of plane p-5 at the tile site
+  QRegs qr;
+  FRegs fr;
+  fetch_q(wrapi(zb - 4, g.nz), qr);
+  // one iteration of the march (Q plane p newest); `prev` holds the stash
+  // of plane p-4, `cur` receives that of plane p-3
+  auto iteration = [&](int p, Stash& prev, Stash& cur) {
+    // slot s5(p) = s5(p-5) was last read by the predictor of iteration p-1
     __syncthreads();
-    stress_plane(0, 0, 0, 0, 0);
-    __syncthreads();
-    lb_plane(0, 0, 0, 0, 0, true, &fr);
-    __syncthreads();
-    Stash st;
-    pred_plane(0, 0, 0, 0, 0, 0, 0, st);
-    __syncthreads();
-    const Sym<QT> pc = qp_of(st);
-    corr_site(0, 0, st, pc, pc, pc);
-  } else {
-    const int zb = bz * zc;
-    const int ze = min(zb + zc, g.nz);
-    // ring slots of plane p (p >= zb - 8 > -2^30)
-    auto s5 = [](int p) { return (p + (1 << 30)) % 5; };
-    auto s3 = [](int p) { return (p + (1 << 30)) % 3; };
-    auto s2 = [](int p) { return (p + (1 << 30)) & 1; };
-    Sym<QT> pm = sym_zero<QT>();  // Q^P of plane p-5 at the tile site
-    QRegs qr;
-    FRegs fr;
-    fetch_q(wrapi(zb - 4, g.nz), qr);
-    // one iteration of the march (Q plane p newest); `prev` holds the stash
-    // of plane p-4, `cur` receives that of plane p-3
-    auto iteration = [&](int p, Stash& prev, Stash& cur) {
-      // slot s5(p) = s5(p-5) was last read by the predictor of iteration p-1
-      __syncthreads();
-      if constexpr (PF) {
-        store_q(s5(p), qr);
-        if (p + 1 <= ze + 3) fetch_q(wrapi(p + 1, g.nz), qr);
-      } else {
-        load_q(s5(p), wrapi(p, g.nz));
-      }
-      __syncthreads();
-      if (p - 1 >= zb - 3) stress_plane(s5(p - 1), s5(p), s5(p - 2), s2(p - 1), s3(p - 1));
-      __syncthreads();
-      if (p - 2 >= zb - 2)
-        lb_plane(p - 2, s2(p - 2), s3(p - 1), s3(p - 3), s3(p - 2), p - 2 >= zb && p - 2 < ze, PF ? &fr : nullptr);
-      // populations of the next moment plane, p - 1
-      if (PF && p - 1 >= zb - 2 && p - 1 <= ze + 1) fetch_f(p - 1, fr);
-      __syncthreads();
-      if (p - 3 >= zb - 1)
-        pred_plane(s5(p - 3), s5(p - 2), s5(p - 4), s3(p - 3), s3(p - 2), s3(p - 4), s2(p - 3), cur);
-      const Sym<QT> pc = qp_of(prev);  // Q^P of plane p-4
-      if (p - 4 >= zb) corr_site(wrapi(p - 4, g.nz), s2(p - 4), prev, pc, qp_of(cur), pm);
-      pm = pc;
-    };
-    // two planes per trip, so the two stashes swap roles without copies
-    Stash stA{}, stB{};
-    int p = zb - 4;
-    for (; p + 1 <= ze + 3; p += 2) {
-      iteration(p, stA, stB);
-      iteration(p + 1, stB, stA);
+    if constexpr (PF) {
+      store_q(s5(p), qr);
+      if (p + 1 <= ze + 3) fetch_q(wrapi(p + 1, g.nz), qr);
+    } else {
+      load_q(s5(p), wrapi(p, g.nz));
     }
-    if (p <= ze + 3) iteration(p, stA, stB);
+    __syncthreads();
+    if (p - 1 >= zb - 3) stress_plane(s5(p - 1), s5(p), s5(p - 2), s2(p - 1), s3(p - 1));
+    __syncthreads();
+    if (p - 2 >= zb - 2)
+      lb_plane(p - 2, s2(p - 2), s3(p - 1), s3(p - 3), s3(p - 2), p - 2 >= zb && p - 2 < ze, PF ? &fr : nullptr);
+    // populations of the next moment plane, p - 1
+    if (PF && p - 1 >= zb - 2 && p - 1 <= ze + 1) fetch_f(p - 1, fr);
+    __syncthreads();
+    if (p - 3 >= zb - 1)
+      pred_plane(s5(p - 3), s5(p - 2), s5(p - 4), s3(p - 3), s3(p - 2), s3(p - 4), s2(p - 3), cur);
+    const Sym<QT> pc = qp_of(prev);  // Q^P of plane p-4
+    if (p - 4 >= zb) corr_site(wrapi(p - 4, g.nz), s2(p - 4), prev, pc, qp_of(cur), pm);
+    pm = pc;
+  };
+  // two planes per trip, so the two stashes swap roles without copies
+  Stash stA{}, stB{};
+  int p = zb - 4;
+  for (; p + 1 <= ze + 3; p += 2) {
+    iteration(p, stA, stB);
+    iteration(p + 1, stB, stA);
   }
+  if (p <= ze + 3) iteration(p, stA, stB);
 }
 
-template <int LAT, typename S, bool DEV, int TX, int TY, int NTHR, bool MRT, typename QT, bool SR,
-          int ST = STENCIL_COMPACT>
+template <typename S, bool DEV, int TX, int TY, int NTHR, bool MRT, typename QT, bool SR>
 __global__ void __launch_bounds__(NTHR)
     fused_step(const QT* __restrict__ Qin, const S* __restrict__ fin, S* __restrict__ fout, QT* __restrict__ Qout,
                GridDims g, Coef<S> c, Coef<QT> cq, int zc, uint32_t srkey) {
   const int nb = gridDim.x * gridDim.y * gridDim.z;
   const int t = xcd_remap(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), nb);
-  fused_body<LAT, S, DEV, TX, TY, NTHR, MRT, QT, SR, ST>(Qin, fin, fout, Qout, g, c, cq, zc, t % gridDim.x,
-                                               (t / gridDim.x) % gridDim.y, t / (gridDim.x * gridDim.y), srkey);
+  fused_body<S, DEV, TX, TY, NTHR, MRT, QT, SR>(Qin, fin, fout, Qout, g, c, cq, zc, t % gridDim.x,
+                                                (t / gridDim.x) % gridDim.y, t / (gridDim.x * gridDim.y), srkey);
 }
 
 }  // namespace lc

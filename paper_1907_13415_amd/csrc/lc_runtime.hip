@@ -15,6 +15,7 @@
 #include "lc_aux.h"
 #include "lc_split.h"
 #include "lc_fused.h"
+#include "lc_fused2d.h"
 #include "lc_batch.h"
 #include "lc_vjp.h"
 #include "lc_runtime.h"
@@ -403,67 +404,79 @@ static void step_split_ptrs(lc_ctx* c, hipStream_t st, bool mark, const Chunks& 
   ctx_end(c, st, e, 1);
 }
 
-// One launch of the single pass with tile TX x TY and NTHR threads.
-template <int LAT, typename S, bool DEV, typename QT, int TX, int TY, int NTHR>
-static void launch_fused(lc_ctx* c, hipStream_t st, int zc, const S* f0, const QT* q0, S* f1, QT* q1) {
+// One launch of the single pass in 3D with chunks of zc planes.
+template <typename S, bool DEV, typename QT, bool MRT, bool SR>
+static void launch_fused3d(lc_ctx* c, hipStream_t st, int zc, const S* f0, const QT* q0, S* f1, QT* q1) {
+  using C = FusedCfg<QT>;
   const GridDims gd{c->g.nx, c->g.ny, c->g.nz, c->L.N};
-  const Coef<S> k = ctx_coef<S>(c);
-  const Coef<QT> kq = ctx_coef<QT>(c);
-  const dim3 grid((c->g.nx + TX - 1) / TX, (c->g.ny + TY - 1) / TY, unsigned((c->g.nz + zc - 1) / zc));
-  constexpr bool F32 = std::is_same<QT, float>::value;
-  const bool sr = F32 && c->g.precision == LC_FP32_SR;
-  const uint32_t key = step_key(c->step);
-  // the isotropic stencils: two-dimensional grids, FP64 and the FP32
-  // deviation form (lc_set_stencil), BGK or MRT
-  if constexpr (Lattice<LAT>::dim == 2 && std::is_same<S, QT>::value) {
+  const dim3 grid((c->g.nx + C::TX - 1) / C::TX, (c->g.ny + C::TY - 1) / C::TY, unsigned((c->g.nz + zc - 1) / zc));
+  hipLaunchKernelGGL((fused_step<S, DEV, C::TX, C::TY, C::NTHR, MRT, QT, SR>), grid, dim3(C::NTHR), 0, st, q0, f0, f1,
+                     q1, gd, ctx_coef<S>(c), ctx_coef<QT>(c), zc, step_key(c->step));
+}
+
+// One launch of the single pass in 2D with tile shape V; the isotropic
+// stencils are provided in FP64 and the FP32 deviation form (lc_set_stencil).
+template <typename S, bool DEV, typename QT, bool MRT, bool SR, int V>
+static void launch_fused2d(lc_ctx* c, hipStream_t st, const S* f0, const QT* q0, S* f1, QT* q1) {
+  constexpr int TX = fused2d_tx(V), TY = fused2d_ty(V);
+  const GridDims gd{c->g.nx, c->g.ny, 1, c->L.N};
+  const dim3 grid((c->g.nx + TX - 1) / TX, (c->g.ny + TY - 1) / TY);
+  if constexpr (std::is_same<S, QT>::value && !SR) {
     if (c->stencil == LC_STENCIL_ISOTROPIC) {
-      if (c->coll == LC_COLL_MRT)
-        hipLaunchKernelGGL((fused_step<LAT, S, DEV, TX, TY, NTHR, true, QT, false, STENCIL_ISO>), grid, dim3(NTHR), 0,
-                           st, q0, f0, f1, q1, gd, k, kq, zc, key);
-      else
-        hipLaunchKernelGGL((fused_step<LAT, S, DEV, TX, TY, NTHR, false, QT, false, STENCIL_ISO>), grid, dim3(NTHR),
-                           0, st, q0, f0, f1, q1, gd, k, kq, zc, key);
+      hipLaunchKernelGGL((fused2d_step<S, DEV, TX, TY, MRT, QT, false, STENCIL_ISO>), grid, dim3(FUSED2D_NTHR), 0, st,
+                         q0, f0, f1, q1, gd, ctx_coef<S>(c), ctx_coef<QT>(c), 0u);
       return;
     }
   }
-  if (c->coll == LC_COLL_MRT) {
-    if (sr)
-      hipLaunchKernelGGL((fused_step<LAT, S, DEV, TX, TY, NTHR, true, QT, F32>), grid, dim3(NTHR), 0, st, q0, f0, f1,
-                         q1, gd, k, kq, zc, key);
-    else
-      hipLaunchKernelGGL((fused_step<LAT, S, DEV, TX, TY, NTHR, true, QT, false>), grid, dim3(NTHR), 0, st, q0, f0,
-                         f1, q1, gd, k, kq, zc, key);
+  hipLaunchKernelGGL((fused2d_step<S, DEV, TX, TY, MRT, QT, SR>), grid, dim3(FUSED2D_NTHR), 0, st, q0, f0, f1, q1, gd,
+                     ctx_coef<S>(c), ctx_coef<QT>(c), step_key(c->step));
+}
+
+// The tile shape of the single pass on a 2D grid: the smallest with which
+// every tile has a CU of its own, else the largest (lc_fused2d.h).
+static int fused2d_shape(const lc_grid& g) {
+  for (int v = 0; v < FUSED2D_NV; v++)
+    if (int64_t((g.nx + fused2d_tx(v) - 1) / fused2d_tx(v)) * ((g.ny + fused2d_ty(v) - 1) / fused2d_ty(v)) <=
+        FUSED2D_CUS)
+      return v;
+  return FUSED2D_NV - 1;
+}
+
+// One step of the single pass between explicit buffers on stream st.
+template <int LAT, typename S, bool DEV, typename QT, bool MRT, bool SR>
+static void step_fused_form(lc_ctx* c, hipStream_t st, const S* f0, const QT* q0, S* f1, QT* q1) {
+  if constexpr (Lattice<LAT>::dim == 3) {
+    using C = FusedCfg<QT>;
+    const int64_t tiles = int64_t((c->g.nx + C::TX - 1) / C::TX) * ((c->g.ny + C::TY - 1) / C::TY);
+    const int zc = c->zchunk > 0 ? std::min(c->zchunk, c->g.nz) : pick_chunk(c->g.nz, tiles, C::ZC, 8, 1);
+    launch_fused3d<S, DEV, QT, MRT, SR>(c, st, zc, f0, q0, f1, q1);
   } else {
-    if (sr)
-      hipLaunchKernelGGL((fused_step<LAT, S, DEV, TX, TY, NTHR, false, QT, F32>), grid, dim3(NTHR), 0, st, q0, f0,
-                         f1, q1, gd, k, kq, zc, key);
-    else
-      hipLaunchKernelGGL((fused_step<LAT, S, DEV, TX, TY, NTHR, false, QT, false>), grid, dim3(NTHR), 0, st, q0, f0,
-                         f1, q1, gd, k, kq, zc, key);
+    static_assert(FUSED2D_NV == 5, "one launch branch per tile shape");
+    switch (fused2d_shape(c->g)) {
+      case 0: launch_fused2d<S, DEV, QT, MRT, SR, 0>(c, st, f0, q0, f1, q1); break;
+      case 1: launch_fused2d<S, DEV, QT, MRT, SR, 1>(c, st, f0, q0, f1, q1); break;
+      case 2: launch_fused2d<S, DEV, QT, MRT, SR, 2>(c, st, f0, q0, f1, q1); break;
+      case 3: launch_fused2d<S, DEV, QT, MRT, SR, 3>(c, st, f0, q0, f1, q1); break;
+      default: launch_fused2d<S, DEV, QT, MRT, SR, 4>(c, st, f0, q0, f1, q1); break;
+    }
   }
 }
 
-// One step of the single pass between explicit buffers on stream st.  On a
-// two-dimensional grid the tile shape and threads per tile follow from the
-// number of tiles (FUSED2D_* in lc_fused.h).
 template <int LAT, typename S, bool DEV, typename QT = S>
 static void step_fused_ptrs(lc_ctx* c, hipStream_t st, bool mark, const S* f0, const QT* q0, S* f1, QT* q1) {
-  using C = FusedCfg<LAT, QT>;
+  constexpr bool F32 = std::is_same<QT, float>::value;
+  const bool mrt = c->coll == LC_COLL_MRT;
   hipEvent_t e = mark ? ctx_begin(c, st) : nullptr;
-  if constexpr (C::d3) {
-    const int64_t tiles = int64_t((c->g.nx + C::TX - 1) / C::TX) * ((c->g.ny + C::TY - 1) / C::TY);
-    const int zc = c->zchunk > 0 ? std::min(c->zchunk, c->g.nz) : pick_chunk(c->g.nz, tiles, C::ZC, 8, 1);
-    launch_fused<LAT, S, DEV, QT, C::TX, C::TY, C::NTHR>(c, st, zc, f0, q0, f1, q1);
-  } else {
-    auto tiles = [&](int tx, int ty) { return int64_t((c->g.nx + tx - 1) / tx) * ((c->g.ny + ty - 1) / ty); };
-    if (tiles(FUSED2D_SMALL_TX, FUSED2D_SMALL_TY) <= FUSED2D_CUS)
-      launch_fused<LAT, S, DEV, QT, FUSED2D_SMALL_TX, FUSED2D_SMALL_TY, FUSED2D_SMALL_NTHR>(c, st, 1, f0, q0, f1, q1);
-    else if (tiles(FUSED2D_MID_TX, FUSED2D_MID_TY) <= FUSED2D_CUS)
-      launch_fused<LAT, S, DEV, QT, FUSED2D_MID_TX, FUSED2D_MID_TY, FUSED2D_MID_NTHR>(c, st, 1, f0, q0, f1, q1);
-    else if (tiles(FUSED2D_HALF_TX, FUSED2D_HALF_TY) <= 4 * FUSED2D_CUS)
-      launch_fused<LAT, S, DEV, QT, FUSED2D_HALF_TX, FUSED2D_HALF_TY, FUSED2D_HALF_NTHR>(c, st, 1, f0, q0, f1, q1);
+  if (F32 && c->g.precision == LC_FP32_SR) {
+    if (mrt)
+      step_fused_form<LAT, S, DEV, QT, true, F32>(c, st, f0, q0, f1, q1);
     else
-      launch_fused<LAT, S, DEV, QT, FUSED2D_WIDE_TX, FUSED2D_WIDE_TY, FUSED2D_WIDE_NTHR>(c, st, 1, f0, q0, f1, q1);
+      step_fused_form<LAT, S, DEV, QT, false, F32>(c, st, f0, q0, f1, q1);
+  } else {
+    if (mrt)
+      step_fused_form<LAT, S, DEV, QT, true, false>(c, st, f0, q0, f1, q1);
+    else
+      step_fused_form<LAT, S, DEV, QT, false, false>(c, st, f0, q0, f1, q1);
   }
   ctx_end(c, st, e, 0);
 }

@@ -179,9 +179,10 @@ __device__ __forceinline__ void body_force(const S* __restrict__ tau, int64_t N,
 // the deviation rho - 1 as summed, which the collision uses for the
 // density part of f_eq (forming it again as rho - 1 from the rounded rho
 // would lose the deviation's low bits at every site and step).
+// moment_sums takes the part that needs the populations alone (inv = 1/rho),
+// velocity the rest.
 template <int LAT, typename S, bool DEV>
-__device__ __forceinline__ void moments(const S (&f)[Lattice<LAT>::q], const S (&F)[3], S& rho, S (&u)[3],
-                                        S& mass) {
+__device__ __forceinline__ void moment_sums(const S (&f)[Lattice<LAT>::q], S& rho, S& mass, S (&j)[3], S& inv) {
   using L = Lattice<LAT>;
   S m = S(0), jx = S(0), jy = S(0), jz = S(0);
 #pragma unroll
@@ -196,10 +197,25 @@ __device__ __forceinline__ void moments(const S (&f)[Lattice<LAT>::q], const S (
   }
   mass = m;
   rho = DEV ? S(1) + m : m;
-  const S inv = S(1) / rho;
-  u[0] = (jx + S(0.5) * F[0]) * inv;
-  u[1] = (jy + S(0.5) * F[1]) * inv;
-  u[2] = L::dim == 3 ? (jz + S(0.5) * F[2]) * inv : S(0);
+  inv = S(1) / rho;
+  j[0] = jx;
+  j[1] = jy;
+  j[2] = jz;
+}
+
+template <int LAT, typename S>
+__device__ __forceinline__ void velocity(const S (&j)[3], const S (&F)[3], S inv, S (&u)[3]) {
+  u[0] = (j[0] + S(0.5) * F[0]) * inv;
+  u[1] = (j[1] + S(0.5) * F[1]) * inv;
+  u[2] = Lattice<LAT>::dim == 3 ? (j[2] + S(0.5) * F[2]) * inv : S(0);
+}
+
+template <int LAT, typename S, bool DEV>
+__device__ __forceinline__ void moments(const S (&f)[Lattice<LAT>::q], const S (&F)[3], S& rho, S (&u)[3],
+                                        S& mass) {
+  S j[3], inv;
+  moment_sums<LAT, S, DEV>(f, rho, mass, j, inv);
+  velocity<LAT, S>(j, F, inv, u);
 }
 
 template <int LAT, typename S, bool DEV>

@@ -1,0 +1,44 @@
+"""The single pass on two-dimensional grids takes its tile shape from the
+number of tiles: grids on either side of each change of shape (16x8, 32x8,
+32x12, 32x16, 32x20 sites, and more tiles than CUs), with and without whole
+tiles, must equal the two sweeps bit for bit in every form."""
+import numpy as np
+import pytest
+
+from paper_1907_13415_amd import inputs
+from gpu_util import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+PARAMS = (1.0, 2.72, 0.05, 0.3, 0.7, 1.3)
+RATES = (1.64, 1.54, 1.9)
+# (nx, ny): 256 and 257 tiles of each shape (nx, ny whole tiles, then ragged)
+SHAPES = [(256, 128), (257, 129), (256, 256), (257, 249), (256, 384), (225, 385), (256, 512), (259, 513), (256, 640),
+          (301, 419), (300, 641), (5, 9), (39, 27)]
+
+
+@pytest.mark.parametrize("nx,ny", SHAPES)
+@pytest.mark.parametrize("precision,mrt,iso", [("fp64", False, False), ("fp32dev", True, False),
+                                               ("fp32sr", False, False), ("mixed", False, False),
+                                               ("fp64", True, True), ("fp32dev", False, True)])
+def test_shape_equals_two_sweeps(nx, ny, precision, mrt, iso):
+    require_gpu()
+    from paper_1907_13415_amd import lc
+    print("fused 2D %dx%d %s mrt %d iso %d" % (nx, ny, precision, mrt, iso), flush=True)
+    rng = np.random.default_rng(nx + ny)
+    q5 = inputs.random_q5((1, ny, nx), rng, amp=0.1)
+    f0 = np.array(lc.lc_lattice_info(lc.LC_D2Q9)[1])[:, None, None, None] * (
+        1 + inputs.random_rel(9, (1, ny, nx), rng, amp=2e-3))
+    out = []
+    for variant in (lc.LC_VARIANT_FUSED, lc.LC_VARIANT_SPLIT):
+        s = lc.Solver("D2Q9", precision, (1, ny, nx), PARAMS)
+        s.set_variant(variant)
+        if mrt:
+            s.set_collision(lc.LC_COLL_MRT, RATES)
+        if iso:
+            s.set_stencil(lc.LC_STENCIL_ISOTROPIC)
+        s.load(q5, f0)
+        s.step(3)
+        out.append((s.export(lc.LC_FIELD_F), s.export(lc.LC_FIELD_Q)))
+    assert np.isfinite(out[0][1]).all()
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
