@@ -26,13 +26,13 @@
 namespace lc {
 
 // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2):
-// hardware block b runs on XCD b % 8.  Remapping b to the logical tile
-// (b % 8) * (nb / 8) + b / 8 gives every XCD one contiguous range of tiles,
-// so neighbouring tiles (which share halo lines) meet in the same L2.
+// hardware block b runs on XCD b % 8.  The remap gives every XCD one
+// contiguous range of the nb logical tiles (the first nb % 8 of them one tile
+// more), so neighbouring tiles (which share halo lines) meet in the same L2.
 constexpr int NUM_XCD = 8;
 __device__ __forceinline__ int xcd_remap(int b, int nb) {
-  if (nb % NUM_XCD != 0) return b;
-  return (b % NUM_XCD) * (nb / NUM_XCD) + b / NUM_XCD;
+  const int xcd = b % NUM_XCD, each = nb / NUM_XCD, more = nb % NUM_XCD;
+  return xcd * each + min(xcd, more) + b / NUM_XCD;
 }
 
 __device__ __forceinline__ int wrapi(int v, int n) {
