@@ -203,13 +203,14 @@ lc_status lc_set_params(lc_ctx *ctx, const lc_params *params);
 /* Choose the kernel variant (LC_VARIANT_*) of the step of Sec. 1.2 (the
  * same arithmetic in each; SPLIT and FUSED agree bit for bit).  AUTO (the
  * default) picks the fastest the library provides for the context's stencil
- * and grid: the two-sweep variant, except FUSED on D2Q9 grids of at most
- * 147456 (384^2) sites with the compact stencils and 65536 (256^2) with the
- * isotropic ones, where launches are latency bound and the single pass
- * measured faster in every precision.  FUSED runs every
+ * and grid: the two-sweep variant on D3Q19, and on D2Q9 FUSED where the grid
+ * fits the chip in one round of tiles (about 400^2 sites) or is large (from
+ * 640^2 sites on), and the faster of the two in between.  FUSED runs every
  * stage of a step in one pass over the grid: a block recomputes the
  * stress, moments and predictor on shrinking rings around its tile instead
- * of reading them back from HBM.  LC_EUNSUPPORTED for the staged variant in
+ * of reading them back from HBM, or on large D2Q9 grids a wave marches
+ * through a strip of columns and evaluates every stage once per site.
+ * LC_EUNSUPPORTED for the staged variant in
  * LC_MIXED. */
 lc_status lc_set_variant(lc_ctx *ctx, int32_t variant);
 

@@ -25,7 +25,7 @@
 //       store of the post-collision populations (pull form);
 //   (d) predictor of plane p-3 on the radius-1 rectangle;
 //   (e) corrector of plane p-4 at the tile's sites, store of Q(n+1).
-// (On two-dimensional grids: lc_fused2d.h.)  Region loops visit the tile's own sites first, in thread order, so the
+// (On two-dimensional grids: lc_fused2d.h, lc_march2d.h.)  Region loops visit the tile's own sites first, in thread order, so the
 // thread that computes a site's predictor also computes its corrector from
 // values it keeps in registers, and the tile's collisions store whole rows.
 #pragma once

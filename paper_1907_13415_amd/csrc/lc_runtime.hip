@@ -16,6 +16,7 @@
 #include "lc_split.h"
 #include "lc_fused.h"
 #include "lc_fused2d.h"
+#include "lc_march2d.h"
 #include "lc_batch.h"
 #include "lc_vjp.h"
 #include "lc_runtime.h"
@@ -434,12 +435,75 @@ static void launch_fused2d(lc_ctx* c, hipStream_t st, const S* f0, const QT* q0,
 
 // The tile shape of the single pass on a 2D grid: the smallest with which
 // every tile has a CU of its own, else the largest (lc_fused2d.h).
+static int64_t fused2d_tiles(const lc_grid& g, int v) {
+  return int64_t((g.nx + fused2d_tx(v) - 1) / fused2d_tx(v)) * ((g.ny + fused2d_ty(v) - 1) / fused2d_ty(v));
+}
 static int fused2d_shape(const lc_grid& g) {
   for (int v = 0; v < FUSED2D_NV; v++)
-    if (int64_t((g.nx + fused2d_tx(v) - 1) / fused2d_tx(v)) * ((g.ny + fused2d_ty(v) - 1) / fused2d_ty(v)) <=
-        FUSED2D_CUS)
-      return v;
+    if (fused2d_tiles(g, v) <= FUSED2D_CUS) return v;
   return FUSED2D_NV - 1;
+}
+static bool fused2d_fits(const lc_grid& g) { return fused2d_tiles(g, FUSED2D_NV - 1) <= FUSED2D_CUS; }
+
+// Rows per chunk of the marching single pass (lc_march2d.h) for grids of
+// nx[k] * ny[k] sites together: the fewest whose waves are on the chip at
+// once.
+template <typename QT>
+static int march_rows(int n, const lc_grid* g) {
+  auto waves = [&](int64_t rows) {
+    int64_t w = 0;
+    for (int k = 0; k < n; k++) w += int64_t((g[k].nx + MARCH_COLS - 1) / MARCH_COLS) * ((g[k].ny + rows - 1) / rows);
+    return w;
+  };
+  int most = 1;
+  for (int k = 0; k < n; k++) most = std::max(most, g[k].ny);
+  int lo = 1, hi = most;  // waves() falls with the rows
+  while (lo < hi) {
+    const int mid = lo + (hi - lo) / 2;
+    if (waves(mid) <= march_waves<QT>())
+      hi = mid;
+    else
+      lo = mid + 1;
+  }
+  return lo;
+}
+
+// Whether the marching single pass takes n 2D grids (one, or the grids of a
+// batch) of at least MARCH_MIN_SITES sites together.  Below that its waves
+// have too few rows each to be worth the eight they repeat: 512^2 in FP32
+// 15.0 us per step against 11.6 in tiles and 13.4 in two sweeps, in FP64 24.1
+// against 21.7 and 22.8; 700^2 20.0 against 24.7 in two sweeps, and 32.7
+// against 38.9; 1400^2 46.6 against 80.7, and 125 against 150.  A strip is 56
+// columns wide: grids that fill less than three quarters of their strips stay
+// in tiles, and so do components beyond 32-bit byte offsets.
+constexpr int64_t MARCH_MIN_SITES = 640 * 640;
+static bool march_takes(int n, const lc_grid* g) {
+  int64_t sites = 0, lanes = 0;
+  for (int k = 0; k < n; k++) {
+    const int64_t N = int64_t(g[k].nx) * g[k].ny;
+    if (N > (int64_t(1) << 32) / 8) return false;
+    sites += N;
+    lanes += int64_t((g[k].nx + MARCH_COLS - 1) / MARCH_COLS) * MARCH_COLS * g[k].ny;
+  }
+  return sites >= MARCH_MIN_SITES && 4 * sites >= 3 * lanes;
+}
+
+// One launch of the marching single pass.
+template <typename S, bool DEV, typename QT, bool MRT, bool SR>
+static void launch_march2d(lc_ctx* c, hipStream_t st, const S* f0, const QT* q0, S* f1, QT* q1) {
+  const GridDims gd{c->g.nx, c->g.ny, 1, c->L.N};
+  const int rows = march_rows<QT>(1, &c->g);
+  const int cols = (c->g.nx + MARCH_COLS - 1) / MARCH_COLS;
+  const dim3 grid(unsigned(cols) * unsigned((c->g.ny + rows - 1) / rows));
+  if constexpr (std::is_same<S, QT>::value && !SR) {
+    if (c->stencil == LC_STENCIL_ISOTROPIC) {
+      hipLaunchKernelGGL((march2d_step<S, DEV, MRT, QT, false, STENCIL_ISO>), grid, dim3(64), 0, st, q0, f0, f1, q1, gd,
+                         ctx_coef<S>(c), ctx_coef<QT>(c), cols, rows, 0u);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((march2d_step<S, DEV, MRT, QT, SR>), grid, dim3(64), 0, st, q0, f0, f1, q1, gd, ctx_coef<S>(c),
+                     ctx_coef<QT>(c), cols, rows, step_key(c->step));
 }
 
 // One step of the single pass between explicit buffers on stream st.
@@ -451,6 +515,10 @@ static void step_fused_form(lc_ctx* c, hipStream_t st, const S* f0, const QT* q0
     const int zc = c->zchunk > 0 ? std::min(c->zchunk, c->g.nz) : pick_chunk(c->g.nz, tiles, C::ZC, 8, 1);
     launch_fused3d<S, DEV, QT, MRT, SR>(c, st, zc, f0, q0, f1, q1);
   } else {
+    if (march_takes(1, &c->g)) {
+      launch_march2d<S, DEV, QT, MRT, SR>(c, st, f0, q0, f1, q1);
+      return;
+    }
     static_assert(FUSED2D_NV == 5, "one launch branch per tile shape");
     switch (fused2d_shape(c->g)) {
       case 0: launch_fused2d<S, DEV, QT, MRT, SR, 0>(c, st, f0, q0, f1, q1); break;
@@ -508,25 +576,21 @@ static lc_status run_steps_split(lc_ctx* c, int64_t n) {
   return hip_check(hipGetLastError(), "step launch");
 }
 
-// The variant a step runs.  AUTO is the two-sweep variant, except the
-// single pass (with the compact stencils) on two-dimensional grids of at
-// most 384^2 sites, whose launches are latency bound and where one launch
-// per step with several threads per tile site measured faster than the two
-// sweeps in every precision (bit-identical results; 256^2: 6.1 against 8.8
-// us in FP32, 7.3 against 9.5 us in FP64; 384^2: 9.3 against 11.1 and 14.5
-// against 14.7 us; from 448^2 the mixed form, from 512^2 FP64 and FP32 with
-// stochastic rounding are faster in two sweeps).
-constexpr int64_t AUTO_FUSED_MAX_SITES = 384 * 384;
-// With the isotropic stencils the single pass measured faster up to 256^2
-// (128^2: 6.1 against 9.3 us in FP32, 7.1 against 10.6 in FP64; 256^2: 7.0
-// against 9.8 and 8.7 against 11.1 us; at 320^2 FP64 is faster in two
-// sweeps).
-constexpr int64_t AUTO_FUSED_MAX_SITES_ISO = 256 * 256;
+// The variant a step runs (bit-identical results).  AUTO takes the two sweeps
+// in 3D.  In 2D it takes the single pass, in tiles where each has a CU of its
+// own (launches are latency bound there: 256^2 5.6 us per step in FP32
+// against 9.0 in two sweeps, 7.1 against 10.0 in FP64; 384^2 8.0 against 11.1
+// and 11.5 against 14.7), marching on large grids (march_takes); in between,
+// up to 640^2 sites, in tiles where Q is float with the compact stencils
+// (512^2 11.6 against 13.4 us), and the two sweeps elsewhere (448^2 in FP64
+// 20.2 against 20.9 us, isotropic in FP32 13.6 against 15.4).
 static int resolved_variant(const lc_ctx* c) {
   if (c->variant != LC_VARIANT_AUTO) return c->variant;
-  if (c->stencil == LC_STENCIL_ISOTROPIC)
-    return c->g.lattice == LC_D2Q9 && c->L.N <= AUTO_FUSED_MAX_SITES_ISO ? LC_VARIANT_FUSED : LC_VARIANT_SPLIT;
-  if (c->g.lattice == LC_D2Q9 && c->L.N <= AUTO_FUSED_MAX_SITES) return LC_VARIANT_FUSED;
+  if (c->g.lattice != LC_D2Q9) return LC_VARIANT_SPLIT;
+  const bool float_q = c->g.precision == LC_FP32_DEV || c->g.precision == LC_FP32_SR;
+  if (fused2d_fits(c->g) || march_takes(1, &c->g) ||
+      (float_q && c->stencil == LC_STENCIL_COMPACT && c->L.N < MARCH_MIN_SITES))
+    return LC_VARIANT_FUSED;
   return LC_VARIANT_SPLIT;
 }
 

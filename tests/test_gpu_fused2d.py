@@ -1,7 +1,8 @@
 """The single pass on two-dimensional grids takes its tile shape from the
-number of tiles: grids on either side of each change of shape (16x8, 32x8,
-32x12, 32x16, 32x20 sites, and more tiles than CUs), with and without whole
-tiles, must equal the two sweeps bit for bit in every form."""
+number of tiles, and marches along y in strips of 56 columns on large grids:
+grids on either side of each change of shape (16x8, 32x8, 32x12, 32x16, 32x20
+sites, more tiles than CUs, strips), with and without whole tiles, strips and
+chunks of rows, must equal the two sweeps bit for bit in every form."""
 import numpy as np
 import pytest
 
@@ -14,7 +15,9 @@ PARAMS = (1.0, 2.72, 0.05, 0.3, 0.7, 1.3)
 RATES = (1.64, 1.54, 1.9)
 # (nx, ny): 256 and 257 tiles of each shape (nx, ny whole tiles, then ragged)
 SHAPES = [(256, 128), (257, 129), (256, 256), (257, 249), (256, 384), (225, 385), (256, 512), (259, 513), (256, 640),
-          (301, 419), (300, 641), (5, 9), (39, 27)]
+          (301, 419), (300, 641), (5, 9), (39, 27),
+          # strips: the smallest grid, whole strips, a last strip of one column, few rows, one chunk of few rows
+          (640, 640), (672, 613), (617, 701), (2000, 205), (65000, 7), (65000, 9)]
 
 
 @pytest.mark.parametrize("nx,ny", SHAPES)
