@@ -404,7 +404,9 @@ lc_status lc_step_static(const lc_grid *grid, const lc_params *params, void *con
  * occupies f_offsets[k] bytes into each f arena (9*N_k values) and
  * q_offsets[k] bytes into each Q arena (5*N_k values, double in the mixed
  * form), in the single-grid layout.  A step of the batch is two kernel launches covering the tiles of
- * every grid; runs of steps are captured once in a HIP graph (64 steps per
+ * every grid, or one of the marching single pass (see lc_set_variant) where
+ * the grids together have 640^2 sites or more (the same results bit for bit);
+ * runs of steps are captured once in a HIP graph (64 steps per
  * graph) and replayed on the batch stream.
  * ------------------------------------------------------------------------- */
 
@@ -435,7 +437,7 @@ lc_status lc_batch_step(lc_batch *b, int64_t n);
 
 /* Select the tile shape of each sweep: v_lb for the stress / LB sweep, v_q
  * for the Q sweep (0: 32x8, 1: 64x4, 2: 16x16, 3: 32x16, 4: 64x8, 5: 64x16,
- * 6: 128x8 sites per block).  Results do not depend on the tile shapes (a
+ * 6: 128x8 sites per block); the batch then runs the two sweeps.  Results do not depend on the tile shapes (a
  * launch shape: implements no passage of the paper).  LC_EINVAL outside
  * 0..6. */
 lc_status lc_batch_set_tiles(lc_batch *b, int32_t v_lb, int32_t v_q);
@@ -460,7 +462,9 @@ lc_status lc_batch_set_stencil(lc_batch *b, int32_t stencil);
 lc_status lc_batch_set_collision(lc_batch *b, int32_t kind, const double *rates, int32_t nrates);
 
 /* Time every pair of tile shapes for trial_steps steps (after one untimed
- * step) with HIP events and keep the fastest; *chosen = v_lb + 7 * v_q.
+ * step) with HIP events and keep the fastest; *chosen = v_lb + 7 * v_q.  The
+ * marching single pass is timed as well and kept if it is faster than every
+ * pair (*ms_per_step is its time then).
  * The state advances by 49 * (trial_steps + 1) steps: tune before loading
  * the real state, or load it again afterwards.  Synchronises the stream.
  * Measurement plumbing: implements no passage of the paper. */

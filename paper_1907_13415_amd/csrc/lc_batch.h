@@ -5,11 +5,12 @@
 // arenas; a descriptor table gives every grid's size, arena offsets and
 // coefficients, and a tile table maps each block of a launch to its grid.
 // One launch of each sweep covers the tiles of all grids, so a time step of
-// the whole batch is two launches, and a run of steps is captured once in a
-// HIP graph and replayed.
+// the whole batch is two launches, or one of the marching single pass
+// (lc_march2d.h) where the grids together are large; a run of steps is
+// captured once in a HIP graph and replayed.
 #pragma once
 
-#include "lc_split.h"
+#include "lc_march2d.h"
 
 namespace lc {
 
@@ -27,7 +28,8 @@ struct BatchDesc {
   int nx, ny;
   int64_t N;
   int64_t f_off, q_off, u_off;  // element offsets into the arenas (f in S, Q and u in QT)
-  int tile0[2], tiles_x[2];     // per sweep (0: LB, 1: Q): first block of this grid, tiles along x
+  int tile0[3], tiles_x[3];     // per sweep (0: LB, 1: Q, 2: march): first block of this grid, tiles (strips) along x
+  int rows;                     // rows per chunk of the march
   Coef<S> c;                    // constants in the population type
   Coef<QT> cq;                  // the same in the order-tensor type
 };
@@ -71,6 +73,23 @@ __global__ void __launch_bounds__(TX* TY)
   const uint32_t key = SR ? step_key(int64_t(*step_base) + step_off) : 0u;
   split_q_body<LAT, QT, TX, TY, SR, ST>(Qa + d.q_off, ua + d.u_off, Qb + d.q_off, g, d.cq, 1, t % d.tiles_x[1],
                                     t / d.tiles_x[1], 0, nullptr, key);
+}
+
+// The step of every grid in one pass, one wave per strip and chunk of rows.
+template <typename S, bool DEV, bool MRT, typename QT, bool SR, int ST>
+__global__ void __launch_bounds__(64)
+    batch_march(const BatchDesc<S, QT>* __restrict__ desc, const int* __restrict__ tile_grid,
+                const QT* __restrict__ Qa, const S* __restrict__ fa, S* __restrict__ fb, QT* __restrict__ Qb,
+                const uint32_t* __restrict__ step_base, int step_off) {
+  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  const int k = tile_grid[b];
+  const BatchDesc<S, QT> d = desc[k];
+  const int t = b - d.tile0[2];
+  const GridDims g{d.nx, d.ny, 1, d.N};
+  const uint32_t key = SR ? step_key(int64_t(*step_base) + step_off) : 0u;
+  const int yb = (t / d.tiles_x[2]) * d.rows;
+  march2d_body<S, DEV, MRT, QT, SR, ST>(Qa + d.q_off, fa + d.f_off, fb + d.f_off, Qb + d.q_off, g, d.c, d.cq,
+                                        (t % d.tiles_x[2]) * MARCH_COLS, yb, min(yb + d.rows, d.ny), key);
 }
 
 // Tile shapes the batch can run with, chosen per sweep by lc_batch_autotune

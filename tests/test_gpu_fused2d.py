@@ -45,3 +45,39 @@ def test_shape_equals_two_sweeps(nx, ny, precision, mrt, iso):
         out.append((s.export(lc.LC_FIELD_F), s.export(lc.LC_FIELD_Q)))
     assert np.isfinite(out[0][1]).all()
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("precision,mrt,iso", [("fp64", True, False), ("fp32dev", False, False),
+                                               ("fp32sr", True, False), ("mixed", False, False),
+                                               ("fp32dev", True, True), ("fp64", False, True)])
+def test_batch_strips_equal_tiles(precision, mrt, iso):
+    """A batch of 640^2 sites or more marches in strips unless tiles are asked
+    for; grids narrower than a strip, of one strip and of many, through a graph
+    of steps and single steps, against the two sweeps bit for bit."""
+    require_gpu()
+    from paper_1907_13415_amd import lc
+    shapes = [(400, 500), (333, 301), (64, 70), (600, 56), (57, 9), (300, 350)]
+    print("batch strips %s mrt %d iso %d" % (precision, mrt, iso), flush=True)
+    params = [(1.0, 2.6 + 0.03 * k, 0.05, 0.3, 0.7, 1.0 + 0.1 * k) for k in range(len(shapes))]
+    q5 = [inputs.random_q5((1,) + s, np.random.default_rng(k), amp=0.05) for k, s in enumerate(shapes)]
+    out = []
+    for tiles in (None, (4, 0), "tuned"):
+        b = lc.BatchSolver(precision, shapes, params)
+        if tiles == (4, 0):
+            b.set_tiles(*tiles)
+        if mrt:
+            b.set_collision(lc.LC_COLL_MRT, RATES)
+        if iso:
+            b.set_stencil(lc.LC_STENCIL_ISOTROPIC)
+        for k, q in enumerate(q5):
+            b.load(k, q)
+        if tiles == "tuned":
+            b.autotune(1)
+            for k, q in enumerate(q5):
+                b.load(k, q)
+        b.step(67)
+        out.append([(b.export(k, lc.LC_FIELD_F), b.export(k, lc.LC_FIELD_Q)) for k in range(len(shapes))])
+    for k in range(len(shapes)):
+        assert np.isfinite(out[0][k][1]).all()
+        for other in out[1:]:
+            assert np.array_equal(out[0][k][0], other[k][0]) and np.array_equal(out[0][k][1], other[k][1]), shapes[k]
