@@ -168,31 +168,43 @@ __device__ __forceinline__ void march2d_body(const QT* __restrict__ Qin, const S
   Rows Q[3], P[3];
   QT t[3][2][2], u[3][2];
   Stash st[3];
-  // Rows in flight, two iterations ahead of their use: a load returns only
+  // Rows in flight, AHEAD iterations before their use: a load returns only
   // after the stores issued before it, and one iteration (about 2 us) is not
-  // always enough (2048^2 in FP32: 142 us with one, 138 us with two).
+  // always enough.  2048^2 sites: FP32 142 us with one, 126 with two and 127
+  // with three; FP64, whose one wave per SIMD has nothing beside it, 258 with
+  // two and 238 with three; 1024^2 in the mixed form 41.7 with two and 43.7
+  // with three.
+  constexpr int AHEAD = sizeof(S) == 8 ? 3 : 2;
   Rows qn[3];
   S f[3][L::q];
-  // periodic indices of rows p-1, p, p+1 and p+2
-  int w0 = wrapi(yb - 4, g.ny), w1 = after(w0), w2 = after(w1), w3 = after(w2);
-  fetch_q(w0, Q[1]);
-  fetch_q(w1, Q[2]);
-  fetch_q(w2, qn[0]);
-  fetch_q(w3, qn[1]);
-  w0 = w1;
-  w1 = w2;
-  w2 = w3;
-  w3 = after(w3);
+  // periodic indices of rows p-3+AHEAD .. p-1+AHEAD (of populations) and
+  // p+AHEAD (of Q)
+  int wq = wrapi(yb - 4, g.ny);
+  fetch_q(wq, Q[1]);
+  fetch_q(wq = after(wq), Q[2]);
+#pragma unroll
+  for (int n = 0; n < AHEAD; n++) fetch_q(wq = after(wq), qn[n]);
+  wq = after(wq);
+  int w0 = wrapi(yb - 3, g.ny), w1 = after(w0), w2 = after(w1);
+  if constexpr (AHEAD == 3) {
+    fetch_f(w0, w1, w2, f[0]);
+    w0 = w1;
+    w1 = w2;
+    w2 = after(w2);
+  }
 
   auto iteration = [&](auto slot, int p) {
     constexpr int K0 = decltype(slot)::value, K1 = (K0 + 1) % 3, K2 = (K0 + 2) % 3;
     Q[K0] = qn[K0];
-    if (p + 2 <= ye + 3) fetch_q(w3, qn[K2]);
-    if (p <= ye + 1) fetch_f(w0, w1, w2, f[K0]);
+    S fc[L::q];
+#pragma unroll
+    for (int i = 0; i < L::q; i++) fc[i] = f[K1][i];
+    if (p + AHEAD <= ye + 3) fetch_q(wq, qn[AHEAD == 3 ? K0 : K2]);
+    if (p + AHEAD <= ye + 3) fetch_f(w0, w1, w2, f[AHEAD == 3 ? K1 : K0]);
+    wq = after(wq);
     w0 = w1;
     w1 = w2;
-    w2 = w3;
-    w3 = after(w3);
+    w2 = after(w2);
 
     // stress of row p-1
     {
@@ -239,7 +251,6 @@ __device__ __forceinline__ void march2d_body(const QT* __restrict__ Qin, const S
           F[a] = S(QT(0.5) * acc);
         }
       }
-      S(&fc)[L::q] = f[K1];
       S rho, mass, us[3];
       moments<0, S, DEV>(fc, F, rho, us, mass);
       u[K1][0] = QT(us[0]);
