@@ -40,10 +40,17 @@ __host__ __device__ constexpr int fused2d_ty(int v) { return v < 2 ? 8 : (v == 2
 // whole stress of the radius-3 rectangle, corners included, is in LDS for the
 // body force, and the stencils of Q, u and Q^P come from the pairs of opposite
 // velocities, with the arithmetic of the two sweeps.
-template <typename S, bool DEV, int TX, int TY, bool MRT, typename QT, bool SR, int ST>
+// REC: record what the reverse step of the step needs (at the tile's sites):
+// the velocity, the density and body force, and the predictor.
+struct StepRecord {
+  double *u, *rho_f, *qp;  // 2, 1 + 2 and 5 components
+};
+
+template <typename S, bool DEV, int TX, int TY, bool MRT, typename QT, bool SR, int ST, bool REC>
 __device__ __forceinline__ void fused2d_body(const QT* __restrict__ Qin, const S* __restrict__ fin,
                                              S* __restrict__ fout, QT* __restrict__ Qout, const GridDims& g,
-                                             const Coef<S>& c, const Coef<QT>& cq, int bx, int by, uint32_t srkey) {
+                                             const Coef<S>& c, const Coef<QT>& cq, int bx, int by, uint32_t srkey,
+                                             const StepRecord& rec) {
   using L = Lattice<0>;
   constexpr int NTHR = FUSED2D_NTHR, NT = TX * TY;
   using R4 = Rect<TX, TY, 4>;
@@ -166,6 +173,14 @@ __device__ __forceinline__ void fused2d_body(const QT* __restrict__ Qin, const S
   S F[3] = {S(0), S(0), S(0)}, u[3] = {S(0), S(0), S(0)};
   auto collide_store = [&]() {
     if (!(kl < NT && x0 + i2 - 2 < g.nx && y0 + j2 - 2 < g.ny)) return;
+    if constexpr (REC) {
+      rec.rho_f[site] = rho;
+#pragma unroll
+      for (int a = 0; a < 2; a++) {
+        rec.u[a * size_t(N) + site] = u[a];
+        rec.rho_f[(a + 1) * size_t(N) + site] = F[a];
+      }
+    }
     if constexpr (MRT)
       collide_mrt<0, S, DEV>(f, rho, mass, u, F, c);
     else
@@ -275,16 +290,20 @@ __device__ __forceinline__ void fused2d_body(const QT* __restrict__ Qin, const S
       stencil_lds<QT, 2, R1::W, R1::N, false>(sP, sP, sP, k1, p, d, Lp);
     const Sym<QT> H = SR ? molecular_field_exact(p, Lp, cq) : molecular_field(p, Lp, cq);
     const Sym<QT> Rp = be_rate_flow<QT, true, 2>(p, H, d, fl, cq);
-    store_q_update<QT, SR>(Qout, N, int64_t(uint32_t(x0 + tx) + sy * uint32_t(y0 + ty)), q, r, Rp, srkey);
+    const int64_t s = int64_t(uint32_t(x0 + tx) + sy * uint32_t(y0 + ty));
+    if constexpr (REC) store_sym(rec.qp, N, s, p);
+    store_q_update<QT, SR>(Qout, N, s, q, r, Rp, srkey);
   }
 }
 
-template <typename S, bool DEV, int TX, int TY, bool MRT, typename QT, bool SR, int ST = STENCIL_COMPACT>
+template <typename S, bool DEV, int TX, int TY, bool MRT, typename QT, bool SR, int ST = STENCIL_COMPACT,
+          bool REC = false>
 __global__ void __launch_bounds__(FUSED2D_NTHR)
     fused2d_step(const QT* __restrict__ Qin, const S* __restrict__ fin, S* __restrict__ fout, QT* __restrict__ Qout,
-                 GridDims g, Coef<S> c, Coef<QT> cq, uint32_t srkey) {
+                 GridDims g, Coef<S> c, Coef<QT> cq, uint32_t srkey, StepRecord rec) {
   const int t = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
-  fused2d_body<S, DEV, TX, TY, MRT, QT, SR, ST>(Qin, fin, fout, Qout, g, c, cq, t % gridDim.x, t / gridDim.x, srkey);
+  fused2d_body<S, DEV, TX, TY, MRT, QT, SR, ST, REC>(Qin, fin, fout, Qout, g, c, cq, t % gridDim.x, t / gridDim.x,
+                                                     srkey, rec);
 }
 
 }  // namespace lc

@@ -128,7 +128,7 @@ Layout layout_of(const lc_grid& g) {
   L.off_vjp = off;
   if (g.lattice == LC_D2Q9 && g.precision == LC_FP64) {
     off = up(off + size_t(VJP_COMPS) * N * 8);
-    off = up(off + size_t(3) * L.nblocks * 3 * 8);
+    off = up(off + size_t(vjp_tiles(g.nx, g.ny)) * 3 * 8);
   }
   L.scratch_bytes = off;
   return L;
@@ -425,12 +425,24 @@ static void launch_fused2d(lc_ctx* c, hipStream_t st, const S* f0, const QT* q0,
   if constexpr (std::is_same<S, QT>::value && !SR) {
     if (c->stencil == LC_STENCIL_ISOTROPIC) {
       hipLaunchKernelGGL((fused2d_step<S, DEV, TX, TY, MRT, QT, false, STENCIL_ISO>), grid, dim3(FUSED2D_NTHR), 0, st,
-                         q0, f0, f1, q1, gd, ctx_coef<S>(c), ctx_coef<QT>(c), 0u);
+                         q0, f0, f1, q1, gd, ctx_coef<S>(c), ctx_coef<QT>(c), 0u, StepRecord{});
       return;
     }
   }
   hipLaunchKernelGGL((fused2d_step<S, DEV, TX, TY, MRT, QT, SR>), grid, dim3(FUSED2D_NTHR), 0, st, q0, f0, f1, q1, gd,
-                     ctx_coef<S>(c), ctx_coef<QT>(c), step_key(c->step));
+                     ctx_coef<S>(c), ctx_coef<QT>(c), step_key(c->step), StepRecord{});
+}
+
+// The same, recording for the reverse step (FP64, BGK, compact stencils).
+template <int V>
+static void launch_fused2d_rec(lc_ctx* c, hipStream_t st, const double* f0, const double* q0, double* f1, double* q1,
+                               const StepRecord& rec) {
+  constexpr int TX = fused2d_tx(V), TY = fused2d_ty(V);
+  const GridDims gd{c->g.nx, c->g.ny, 1, c->L.N};
+  const dim3 grid((c->g.nx + TX - 1) / TX, (c->g.ny + TY - 1) / TY);
+  const Coef<double> k = ctx_coef<double>(c);
+  hipLaunchKernelGGL((fused2d_step<double, false, TX, TY, false, double, false, STENCIL_COMPACT, true>), grid,
+                     dim3(FUSED2D_NTHR), 0, st, q0, f0, f1, q1, gd, k, k, 0u, rec);
 }
 
 // The tile shape of the single pass on a 2D grid: the smallest with which
@@ -932,49 +944,42 @@ static VjpFields vjp_fields(lc_ctx* c) {
   v.F = take(2);
   v.qp = take(5);
   v.r = take(5);
-  v.fbar = take(9);
-  v.qpb = take(5);
-  v.lpb = take(5);
-  v.dqpb = take(10);
-  v.ub = take(2);
-  v.gb = take(4);
-  v.rhob = take(1);
-  v.fb = take(2);
-  v.qb = take(5);
-  v.hb = take(5);
-  v.dqb = take(10);
-  v.lb = take(5);
-  v.nblocks = c->L.nblocks;
+  v.adj_f = take(9);
+  v.adj_q = take(5);
+  v.nblocks = vjp_tiles(c->g.nx, c->g.ny);
   // the partials follow at the next 256-byte boundary, as laid out
   v.part = reinterpret_cast<double*>((reinterpret_cast<uintptr_t>(base + size_t(VJP_COMPS) * N) + 255) &
                                      ~uintptr_t(255));
   return v;
 }
 
-// The reverse kernels of one step, given the forward quantities of that
-// step in v (rho, u, F, predictor); parameter partials accumulate.  With
-// fold, adj_q is assembled inside vjp_r1 from the previous reverse step's
-// gathers; with finish, the gathers are applied to adj_q at the end (the
-// last step of a call).
-static void vjp_reverse(lc_ctx* c, const VjpFields& v, const double* q_n, double* adj_f, double* adj_q, bool fold,
-                        bool finish) {
+// The adjoint buffers of a reverse sweep: each step reads [cur] and writes the
+// other pair; [0] is the caller's.
+struct VjpAdjoint {
+  double *f[2], *q[2];
+  int cur = 0;
+};
+
+// The reverse of one step, given its forward quantities in v (rho, u, F,
+// predictor); parameter partials accumulate.
+static void vjp_reverse(lc_ctx* c, const VjpFields& v, const double* q_n, VjpAdjoint& a) {
   const GridDims gd{c->g.nx, c->g.ny, 1, c->L.N};
-  const Coef<double> k = make_coef<double>(c->p);
-  const dim3 grid = site_grid(c->g), block = site_block();
-  // two threads per site (two halves of each block along z), same tiles
-  static_assert(REV_TX == SITE_TX && REV_TY == SITE_TY, "reverse tiles are the site tiles");
-  const dim3 block2(REV_TX, REV_TY, 2);
-  hipLaunchKernelGGL(vjp_r1, grid, block2, 0, c->stream, adj_f, adj_q, fold ? 1 : 0, v, gd, k);
-  hipLaunchKernelGGL(vjp_r2, grid, block2, 0, c->stream, q_n, adj_q, v, gd, k);
-  hipLaunchKernelGGL(vjp_r34, grid, block2, 0, c->stream, adj_f, q_n, v, gd, k);
-  if (finish) hipLaunchKernelGGL(vjp_r5, grid, block, 0, c->stream, adj_q, v, gd);
+  const dim3 grid((c->g.nx + REV_TX - 1) / REV_TX, (c->g.ny + REV_TY - 1) / REV_TY);
+  hipLaunchKernelGGL(vjp_step, grid, dim3(REV_NTHR), 0, c->stream, a.f[a.cur], a.q[a.cur], a.f[a.cur ^ 1],
+                     a.q[a.cur ^ 1], q_n, v.qp, v.rho, v.u, v.F, v.part, gd, make_coef<double>(c->p));
+  a.cur ^= 1;
 }
 
 static void vjp_begin(lc_ctx* c, const VjpFields& v) {
-  hipLaunchKernelGGL(vjp_zero, dim3(8), dim3(256), 0, c->stream, v.part, 3 * v.nblocks * 3);
+  hipLaunchKernelGGL(vjp_zero, dim3(8), dim3(256), 0, c->stream, v.part, v.nblocks * 3);
 }
 
-static void vjp_end(lc_ctx* c, const VjpFields& v, double* dparams) {
+// The parameter derivatives to the caller, and the adjoint if it ended in the
+// second pair of buffers.
+static void vjp_end(lc_ctx* c, const VjpFields& v, const VjpAdjoint& a, double* dparams) {
+  if (a.cur)
+    hipLaunchKernelGGL(vjp_copy, dim3(unsigned(std::min<int64_t>((9 * c->L.N + 255) / 256, 2048))), dim3(256), 0,
+                       c->stream, a.f[1], a.q[1], a.f[0], a.q[0], c->L.N);
   hipLaunchKernelGGL(vjp_params, dim3(1), dim3(256), 0, c->stream, v.part, v.nblocks, dparams);
 }
 
@@ -990,8 +995,9 @@ static void vjp_launch(lc_ctx* c, const double* f_n, const double* q_n, double* 
   hipLaunchKernelGGL((stage_tau<0, double>), grid, block, 0, c->stream, q_n, v.tau, gd, k);
   hipLaunchKernelGGL(vjp_fwd_moments, grid, block, 0, c->stream, f_n, 0, v.tau, v, gd);
   hipLaunchKernelGGL((stage_pred<0, double>), grid, block, 0, c->stream, q_n, v.u, v.qp, v.r, gd, k);
-  vjp_reverse(c, v, q_n, adj_f, adj_q, false, true);
-  vjp_end(c, v, dparams);
+  VjpAdjoint a{{adj_f, v.adj_f}, {adj_q, v.adj_q}};
+  vjp_reverse(c, v, q_n, a);
+  vjp_end(c, v, a, dparams);
 }
 
 static lc_status vjp_check(lc_ctx* c) {
@@ -1042,24 +1048,39 @@ struct VjpHist {
   double* p(int j) const { return slot(j) + 19 * size_t(N); }
 };
 
-// Replay n steps from a checkpoint on stream st, recording every step.
-static void vjp_replay(lc_ctx* c, hipStream_t st, const double* f_ck, const double* q_ck, int n, const VjpHist& H) {
+// Replay of a segment from its checkpoint on stream st: the state of step 0,
+// then step j into slot j + 1, recorded.  As the forward step: one pass where
+// every tile has a CU of its own (256^2: 7.4 us per step, recording included,
+// against 11.1 in two sweeps).
+static void vjp_replay_begin(lc_ctx* c, hipStream_t st, const double* f_ck, const double* q_ck, const VjpHist& H) {
   const GridDims gd{c->g.nx, c->g.ny, 1, c->L.N};
   hipLaunchKernelGGL((load_state<0, double, false>), site_grid(c->g), site_block(), 0, st, f_ck, q_ck, H.f(0),
                      H.q(0), gd);
-  for (int j = 0; j < n; j++)
-    step_split_ptrs<0, double, false>(c, st, false, Chunks{1, 1}, H.f(j), H.q(j), H.f(j + 1), H.q(j + 1), H.u(j), H.r(j), H.p(j));
 }
 
-// The reverse steps n-1 .. 0 of a recorded segment on the context stream.
-static void vjp_walk(lc_ctx* c, VjpFields& v, int n, const VjpHist& H, double* adj_f, double* adj_q) {
-  for (int j = n - 1; j >= 0; j--) {
-    v.u = H.u(j);
-    v.rho = H.r(j);
-    v.F = H.r(j) + H.N;
-    v.qp = H.p(j);
-    vjp_reverse(c, v, H.q(j), adj_f, adj_q, j < n - 1, j == 0);
+static void vjp_replay_step(lc_ctx* c, hipStream_t st, int j, const VjpHist& H) {
+  const double *f0 = H.f(j), *q0 = H.q(j);
+  double *f1 = H.f(j + 1), *q1 = H.q(j + 1);
+  const StepRecord rec{H.u(j), H.r(j), H.p(j)};
+  static_assert(FUSED2D_NV == 5, "one launch branch per tile shape");
+  switch (fused2d_fits(c->g) ? fused2d_shape(c->g) : -1) {
+    case 0: launch_fused2d_rec<0>(c, st, f0, q0, f1, q1, rec); break;
+    case 1: launch_fused2d_rec<1>(c, st, f0, q0, f1, q1, rec); break;
+    case 2: launch_fused2d_rec<2>(c, st, f0, q0, f1, q1, rec); break;
+    case 3: launch_fused2d_rec<3>(c, st, f0, q0, f1, q1, rec); break;
+    case 4: launch_fused2d_rec<4>(c, st, f0, q0, f1, q1, rec); break;
+    default:
+      step_split_ptrs<0, double, false>(c, st, false, Chunks{1, 1}, f0, q0, f1, q1, rec.u, rec.rho_f, rec.qp);
   }
+}
+
+// The reverse of step j of a recorded segment on the context stream.
+static void vjp_walk_step(lc_ctx* c, VjpFields& v, int j, const VjpHist& H, VjpAdjoint& a) {
+  v.u = H.u(j);
+  v.rho = H.r(j);
+  v.F = H.r(j) + H.N;
+  v.qp = H.p(j);
+  vjp_reverse(c, v, H.q(j), a);
 }
 
 static size_t up256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -1076,11 +1097,13 @@ lc_status lc_vjp_segment(lc_ctx* c, const double* f_ck, const double* q_ck, int3
   if (st) return st;
   if (reinterpret_cast<uintptr_t>(hist) & 255) return fail(LC_EINVAL, "history must be 256-byte aligned");
   const VjpHist H{static_cast<double*>(hist), c->L.N};
-  vjp_replay(c, c->stream, f_ck, q_ck, n, H);
+  vjp_replay_begin(c, c->stream, f_ck, q_ck, H);
+  for (int j = 0; j < n; j++) vjp_replay_step(c, c->stream, j, H);
   VjpFields v = vjp_fields(c);
   vjp_begin(c, v);
-  vjp_walk(c, v, n, H, adj_f, adj_q);
-  vjp_end(c, v, dparams);
+  VjpAdjoint a{{adj_f, v.adj_f}, {adj_q, v.adj_q}};
+  for (int j = n - 1; j >= 0; j--) vjp_walk_step(c, v, j, H, a);
+  vjp_end(c, v, a, dparams);
   // the context's own state is untouched
   return hip_check(hipGetLastError(), "reverse segment launch");
 }
@@ -1127,6 +1150,9 @@ lc_status lc_vjp_backward(lc_ctx* c, int32_t nseg, const double* const* f_cks, c
   // Segment k is replayed into half k & 1 on the replay stream while the
   // context stream walks segment k + 1 back: events vev[0..1] mark a replay
   // done, vev[2..3] a walk done (per half), vev[4] the caller's prior work.
+  // The steps of the two are enqueued in turn: a launch takes the host 3 to 4
+  // us, so one stream's whole segment enqueued first would leave the other
+  // stream waiting for the host and not for its data.
   hipEvent_t* rep = c->vev;
   hipEvent_t* walk = c->vev + 2;
   hipEvent_t entry = c->vev[4];
@@ -1134,21 +1160,24 @@ lc_status lc_vjp_backward(lc_ctx* c, int32_t nseg, const double* const* f_cks, c
   bool ok = chk(hipEventRecord(entry, c->stream)) && chk(hipStreamWaitEvent(c->aux, entry, 0));
   VjpFields v = vjp_fields(c);
   vjp_begin(c, v);
+  VjpAdjoint a{{adj_f, v.adj_f}, {adj_q, v.adj_q}};
   for (int32_t k = nseg - 1; ok && k >= -1; k--) {
-    if (k >= 0) {
+    const int32_t w = k + 1;  // the segment walked in this pass
+    const int nw = w < nseg ? ns[w] : 0, nr = k >= 0 ? ns[k] : 0;
+    if (nw) ok = ok && chk(hipStreamWaitEvent(c->stream, rep[w & 1], 0));
+    if (nr) {
       // replay segment k once the walk that last used its half is done
       if (k + 2 < nseg) ok = ok && chk(hipStreamWaitEvent(c->aux, walk[k & 1], 0));
-      vjp_replay(c, c->aux, f_cks[k], q_cks[k], ns[k], H[k & 1]);
-      ok = ok && chk(hipEventRecord(rep[k & 1], c->aux));
+      vjp_replay_begin(c, c->aux, f_cks[k], q_cks[k], H[k & 1]);
     }
-    const int32_t w = k + 1;  // the segment walked in this pass
-    if (w < nseg) {
-      ok = ok && chk(hipStreamWaitEvent(c->stream, rep[w & 1], 0));
-      vjp_walk(c, v, ns[w], H[w & 1], adj_f, adj_q);
-      ok = ok && chk(hipEventRecord(walk[w & 1], c->stream));
+    for (int j = 0; j < std::max(nw, nr); j++) {
+      if (j < nw) vjp_walk_step(c, v, nw - 1 - j, H[w & 1], a);
+      if (j < nr) vjp_replay_step(c, c->aux, j, H[k & 1]);
     }
+    if (nw) ok = ok && chk(hipEventRecord(walk[w & 1], c->stream));
+    if (nr) ok = ok && chk(hipEventRecord(rep[k & 1], c->aux));
   }
-  vjp_end(c, v, dparams);
+  vjp_end(c, v, a, dparams);
   if (!ok) return fail(LC_EDEVICE, "stream ordering of the reverse sweep failed");
   return hip_check(hipGetLastError(), "reverse sweep launch");
 }
