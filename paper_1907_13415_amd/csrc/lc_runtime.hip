@@ -565,8 +565,60 @@ static void step_fused_ptrs(lc_ctx* c, hipStream_t st, bool mark, const S* f0, c
   ctx_end(c, st, e, 0);
 }
 
+// One launch of two steps (fused2d_pair).
+template <typename S, bool DEV, typename QT, bool MRT, bool SR>
+static void launch_fused2d_pair(lc_ctx* c, const S* f0, const QT* q0, S* f1, QT* q1) {
+  constexpr int TX = FUSED2D_PAIR_TX, TY = FUSED2D_PAIR_TY;
+  const GridDims gd{c->g.nx, c->g.ny, 1, c->L.N};
+  const dim3 grid((c->g.nx + TX - 1) / TX, (c->g.ny + TY - 1) / TY);
+  const Coef<S> k = ctx_coef<S>(c);
+  const Coef<QT> kq = ctx_coef<QT>(c);
+  if constexpr (std::is_same<S, float>::value && std::is_same<QT, float>::value && !SR) {
+    if (c->stencil == LC_STENCIL_ISOTROPIC) {
+      hipLaunchKernelGGL((fused2d_pair<S, DEV, MRT, QT, false, STENCIL_ISO>), grid, dim3(FUSED2D_NTHR), 0, c->stream,
+                         q0, f0, f1, q1, gd, k, kq, 0u, 0u);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((fused2d_pair<S, DEV, MRT, QT, SR>), grid, dim3(FUSED2D_NTHR), 0, c->stream, q0, f0, f1, q1, gd,
+                     k, kq, step_key(c->step), step_key(c->step + 1));
+}
+
+// Steps of the single pass.  On 2D grids of at most one 16x8 tile per CU two
+// steps go in a launch, two launches at a time, so that the state after n
+// steps is in the buffers that n single steps would leave it in; launches that
+// are timed one by one are single steps, and so are those of FP64 with the
+// isotropic stencils, whose larger first step spills (64^2 6.6 us per step in
+// pairs against 6.2).
 template <int LAT, typename S, bool DEV, typename QT = S>
 static lc_status run_steps_fused(lc_ctx* c, int64_t n) {
+  constexpr bool F32 = std::is_same<QT, float>::value;
+  const bool sr = F32 && c->g.precision == LC_FP32_SR, mrt = c->coll == LC_COLL_MRT;
+  if constexpr (Lattice<LAT>::dim == 2) {
+    const bool spills = sizeof(S) == 8 && c->stencil == LC_STENCIL_ISOTROPIC;
+    if (!c->timing && !spills && fused2d_shape(c->g) == 0) {
+      for (; n >= 4; n -= 4)
+        for (int half = 0; half < 2; half++) {
+          const S* f0 = static_cast<const S*>(c->b.f[c->parity]);
+          const QT* q0 = static_cast<const QT*>(c->b.Q[c->parity]);
+          S* f1 = static_cast<S*>(c->b.f[c->parity ^ 1]);
+          QT* q1 = static_cast<QT*>(c->b.Q[c->parity ^ 1]);
+          if (sr) {
+            if (mrt)
+              launch_fused2d_pair<S, DEV, QT, true, F32>(c, f0, q0, f1, q1);
+            else
+              launch_fused2d_pair<S, DEV, QT, false, F32>(c, f0, q0, f1, q1);
+          } else {
+            if (mrt)
+              launch_fused2d_pair<S, DEV, QT, true, false>(c, f0, q0, f1, q1);
+            else
+              launch_fused2d_pair<S, DEV, QT, false, false>(c, f0, q0, f1, q1);
+          }
+          c->parity ^= 1;
+          c->step += 2;
+        }
+    }
+  }
   for (int64_t it = 0; it < n; it++) {
     step_fused_ptrs<LAT, S, DEV, QT>(c, c->stream, true, static_cast<const S*>(c->b.f[c->parity]),
                                      static_cast<const QT*>(c->b.Q[c->parity]),

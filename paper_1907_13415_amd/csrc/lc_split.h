@@ -267,37 +267,44 @@ __device__ __forceinline__ void store_region(const RegionRegs<S, TX, TY, NC>& r,
   }
 }
 
-// Store of Q(n+1) = Q + (R(Q) + R(Q^P))/2 (Sec. 1.2.2, step 5) at site s;
+// Q(n+1) = Q + (R(Q) + R(Q^P))/2 (Sec. 1.2.2, step 5) at site s;
 // with SR the float sums are rounded stochastically, one uniform number per
 // site (from the site index and the step's key) serving its five
 // components (each rounding stays unbiased).
-// STREAM: nontemporal stores, for tiles whose rows are whole cache lines;
-// the strips of lc_march2d.h share their first and last lines with their
-// neighbours and leave them in the cache to be completed (1400^2 in FP32:
-// 46.6 us per step against 58.0 with nontemporal stores).
+// put(k, v) takes component k.
+template <typename S, bool SR, typename PUT>
+__device__ __forceinline__ void q_update(uint32_t s, const Sym<S>& q, const Sym<S>& r, const Sym<S>& rp, uint32_t srkey,
+                                         PUT put) {
+  if constexpr (SR) {
+    const float u = site_uniform(s, srkey);
+    put(0, add_stochastic(q.xx, S(0.5) * (r.xx + rp.xx), u));
+    put(1, add_stochastic(q.xy, S(0.5) * (r.xy + rp.xy), u));
+    put(2, add_stochastic(q.xz, S(0.5) * (r.xz + rp.xz), u));
+    put(3, add_stochastic(q.yy, S(0.5) * (r.yy + rp.yy), u));
+    put(4, add_stochastic(q.yz, S(0.5) * (r.yz + rp.yz), u));
+  } else {
+    put(0, q.xx + S(0.5) * (r.xx + rp.xx));
+    put(1, q.xy + S(0.5) * (r.xy + rp.xy));
+    put(2, q.xz + S(0.5) * (r.xz + rp.xz));
+    put(3, q.yy + S(0.5) * (r.yy + rp.yy));
+    put(4, q.yz + S(0.5) * (r.yz + rp.yz));
+  }
+}
+
+// The same into memory.  STREAM: nontemporal stores, for tiles whose rows are
+// whole cache lines; the strips of lc_march2d.h share their first and last
+// lines with their neighbours and leave them in the cache to be completed
+// (1400^2 in FP32: 46.6 us per step against 58.0 with nontemporal stores).
 template <typename S, bool SR, bool STREAM = true>
 __device__ __forceinline__ void store_q_update(S* __restrict__ Qout, int64_t N, int64_t s, const Sym<S>& q,
                                                const Sym<S>& r, const Sym<S>& rp, uint32_t srkey) {
-  auto put = [&](S v, S* p) {
+  q_update<S, SR>(uint32_t(s), q, r, rp, srkey, [&](int k, S v) {
+    S* const at = &(Qout + size_t(k) * size_t(N))[uint32_t(s)];
     if constexpr (STREAM)
-      __builtin_nontemporal_store(v, p);
+      __builtin_nontemporal_store(v, at);
     else
-      *p = v;
-  };
-  if constexpr (SR) {
-    const float u = site_uniform(uint32_t(s), srkey);
-    put(add_stochastic(q.xx, S(0.5) * (r.xx + rp.xx), u), &Qout[s]);
-    put(add_stochastic(q.xy, S(0.5) * (r.xy + rp.xy), u), &Qout[N + s]);
-    put(add_stochastic(q.xz, S(0.5) * (r.xz + rp.xz), u), &Qout[2 * N + s]);
-    put(add_stochastic(q.yy, S(0.5) * (r.yy + rp.yy), u), &Qout[3 * N + s]);
-    put(add_stochastic(q.yz, S(0.5) * (r.yz + rp.yz), u), &Qout[4 * N + s]);
-  } else {
-    put(q.xx + S(0.5) * (r.xx + rp.xx), &Qout[s]);
-    put(q.xy + S(0.5) * (r.xy + rp.xy), &Qout[N + s]);
-    put(q.xz + S(0.5) * (r.xz + rp.xz), &Qout[2 * N + s]);
-    put(q.yy + S(0.5) * (r.yy + rp.yy), &Qout[3 * N + s]);
-    put(q.yz + S(0.5) * (r.yz + rp.yz), &Qout[4 * N + s]);
-  }
+      *at = v;
+  });
 }
 
 // ---------------------------------------------------------------------------

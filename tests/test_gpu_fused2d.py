@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 PARAMS = (1.0, 2.72, 0.05, 0.3, 0.7, 1.3)
 RATES = (1.64, 1.54, 1.9)
 # (nx, ny): 256 and 257 tiles of each shape (nx, ny whole tiles, then ragged)
-SHAPES = [(256, 128), (257, 129), (256, 256), (257, 249), (256, 384), (225, 385), (256, 512), (259, 513), (256, 640),
-          (301, 419), (300, 641), (5, 9), (39, 27),
+SHAPES = [(1, 1), (7, 130), (24, 8), (100, 100), (256, 128), (257, 129), (256, 256), (257, 249), (256, 384),
+          (225, 385), (256, 512), (259, 513), (256, 640), (301, 419), (300, 641), (5, 9), (39, 27),
           # strips: the smallest grid, whole strips, a last strip of one column, few rows, one chunk of few rows
           (640, 640), (672, 613), (617, 701), (2000, 205), (65000, 7), (65000, 9)]
 
@@ -41,7 +41,7 @@ def test_shape_equals_two_sweeps(nx, ny, precision, mrt, iso):
         if iso:
             s.set_stencil(lc.LC_STENCIL_ISOTROPIC)
         s.load(q5, f0)
-        s.step(3)
+        s.step(7)  # on the smallest shape two launches of two steps and three of one
         out.append((s.export(lc.LC_FIELD_F), s.export(lc.LC_FIELD_Q)))
     assert np.isfinite(out[0][1]).all()
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
