@@ -291,23 +291,22 @@ static lc_status run_steps_staged(lc_ctx* c, int64_t n) {
 // planes, one after another, so a grid with few tiles is bound by that serial
 // chain while most CUs idle: there shorter chunks win in spite of the planes
 // they compute twice.  The estimate counts, per CU, the marches that run one
-// after another; with two blocks resident (nearly every form of the sweeps) a
-// march beside another on its CU takes 1.4 times as long as alone (measured
-// 1.3-1.6).
+// after another; a march that shares its CU with one other takes 1.4 times as
+// long as alone (measured 1.3-1.6), with two others 1.85 times (Q sweep,
+// 1.8-1.9).
 // Measured on the stress/LB and Q sweeps, long default chunks against the
 // chosen ones: 24^3 FP32 67.7 -> 14.7 and 56.9 -> 11.7 us, 64^3 FP64
 // 80 -> 32 and 147 -> 24 us, 129x100x75 FP32 isotropic 186 -> 95 and
 // 474 -> 111 us; from 256^3 on the chunk is the longest allowed.
 static int pick_chunk(int nz, int64_t tiles, int most, int extra, int resident = 2) {
   constexpr int CUS = 256;
-  constexpr double BESIDE = 1.4;
+  constexpr double BESIDE[4] = {0.0, 1.0, 1.4, 1.85};  // by blocks on the CU
   int best = 1;
   double best_cost = 1e300;
   for (int zc = 1; zc <= std::min(most, nz); zc++) {
     const int64_t blocks = tiles * ((nz + zc - 1) / zc);
     const int64_t full = blocks / (CUS * resident), rest = blocks % (CUS * resident);
-    const double together = resident == 1 ? 1.0 : BESIDE;
-    const double rounds = double(full) * together + (rest == 0 ? 0.0 : (rest <= CUS ? 1.0 : together));
+    const double rounds = double(full) * BESIDE[resident] + BESIDE[(rest + CUS - 1) / CUS];
     const double cost = rounds * (zc + extra);
     if (cost <= best_cost) {
       best_cost = cost;
@@ -346,7 +345,7 @@ static Chunks split_chunks(const lc_ctx* c) {
   const bool wide = sizeof(S) == 4 && (c->coll == LC_COLL_MRT || iso);
   return Chunks{pick_chunk(c->g.nz, iso ? tiles(iso_lb_tx<LAT, S>(), ISO_LB_TY) : tiles(C::LB_TX, C::LB_TY),
                            wide ? 32 : C::ZC_LB, 2),
-                pick_chunk(c->g.nz, tiles(C::Q_TX, C::Q_TY), C::ZC_Q, 2)};
+                pick_chunk(c->g.nz, tiles(C::Q_TX, C::Q_TY), C::ZC_Q, 2, iso ? 2 : 3)};
 }
 
 // One step of the split sweeps between explicit buffers (pull-form

@@ -612,21 +612,28 @@ template <int LAT, typename S, int TX, int TY, bool SR = false, int ST = STENCIL
 __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S* __restrict__ uin,
                                              S* __restrict__ Qout, const GridDims& g, const Coef<S>& c, int zc,
                                              int bx, int by, int bz, S* __restrict__ rec = nullptr,
-                                             uint32_t srkey = 0) {
+                                             uint32_t srkey = 0, bool turn = false) {
   using L = Lattice<LAT>;
   using T = Tile<TX, TY>;
   constexpr int DIM = L::dim;
   // Three LDS planes of Q and u (z-1, z, z+1 of the predictor).  Q^P on
-  // the tile and its ring: in single precision one LDS plane for the
-  // corrector's in-plane neighbours, its centre and z neighbours being the
-  // owner's own predictor values kept in registers; in double precision
-  // (one wave per SIMD, where registers are the scarcer resource) three LDS
-  // planes, z-1, z and z+1 of the corrector.
+  // the tile and its ring: one LDS plane for the corrector's in-plane
+  // neighbours, its centre and z neighbours being the owner's own predictor
+  // values (ZREG).  Registers bound how many blocks share a CU, and so how
+  // much of the chain of LDS reads and barriers is hidden: the owner reads
+  // the Q and u of its corrector from LDS again instead of keeping them, and
+  // the ring's predictor runs after the corrector, when the values kept for
+  // that are dead.  FP32 197 -> 133 registers, two -> three blocks of four
+  // waves per CU; FP64, which held Q^P in three LDS planes, 296 -> 242
+  // registers and 67.7 -> 53.3 KB, two -> three blocks of two waves.
+  // Sweep on 256^3: FP32 337 -> 327 us, FP32 SR 396 -> 370, FP64 697 -> 656,
+  // FP32 isotropic (no spills now) 1019 -> 683; 200x180x150: FP32 145 -> 136,
+  // FP64 274 -> 238.
   // isotropic stencils: the predictor also runs at the ring's corners, and
   // in 3D the corrector reads the predictor's diagonal neighbours in the
   // planes above and below, so three LDS planes of it are kept
   constexpr bool ISO = ST == STENCIL_ISO;
-  constexpr bool ZREG = DIM == 3 && sizeof(S) == 4 && !ISO;
+  constexpr bool ZREG = DIM == 3 && !ISO;
   constexpr int NP = DIM == 3 ? 3 : 1;
   constexpr int NPS = (DIM == 3 && !ZREG) ? 3 : 1;
   constexpr int NC = 5 + DIM;  // Q components then u components
@@ -636,6 +643,7 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
   __shared__ S sP[NPS][5][T::R1];
 
   const int tx = threadIdx.x, ty = threadIdx.y, tid = tx + TX * ty;
+  const int rt = turn ? tid ^ (T::NT / 2) : tid;  // the thread's ring point
   const int x0 = bx * TX, y0 = by * TY;
   const int x = x0 + tx, y = y0 + ty;
   const bool own = x < g.nx && y < g.ny;
@@ -733,7 +741,7 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
         stencil_lds_iso3<S, T::W1, T::R1, false>(sP[b], sP[bzp], sP[bzm], k1, pcc, d, Lp);
       const Sym<S> H = SR ? molecular_field_exact(pcc, Lp, c) : molecular_field(pcc, Lp, c);
       const Sym<S> Rp = be_rate_flow<S, true, DIM>(pcc, H, d, st.fl, c);
-      const int64_t s = x + (int64_t)g.nx * (y + (int64_t)g.ny * z);
+      const int64_t s = uint32_t(x) + uint32_t(g.nx) * (uint32_t(y) + uint32_t(g.ny) * uint32_t(z));
       if (rec) store_sym(rec, N, s, pcc);
       store_q_update<S, SR>(Qout, N, s, st.q, st.r, Rp, srkey);
       return;
@@ -764,7 +772,7 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
     const Sym<S> Lp{lap[0], lap[1], lap[2], lap[3], lap[4]};
     const Sym<S> H = SR ? molecular_field_exact(pc, Lp, c) : molecular_field(pc, Lp, c);
     const Sym<S> Rp = be_rate_flow<S, true, DIM>(pc, H, d, st.fl, c);
-    const int64_t s = x + (int64_t)g.nx * (y + (int64_t)g.ny * z);
+    const int64_t s = uint32_t(x) + uint32_t(g.nx) * (uint32_t(y) + uint32_t(g.ny) * uint32_t(z));
     if (rec) store_sym(rec, N, s, pc);  // record the predictor (reverse-mode replay)
     store_q_update<S, SR>(Qout, N, s, st.q, st.r, Rp, srkey);
   };
@@ -814,19 +822,32 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
       // without ZREG, sP[pslot(p)] was last read by the corrector of
       // iteration p-1, and the predictor values go there at once
       const Sym<S> own_p = pred_point(slot(p), slot(p + 1), slot(p - 1), tx + 1, ty + 1, cur);
-      if constexpr (!ZREG) store_pred(pslot(p), tx + 1, ty + 1, own_p);
-      const bool ring = tid < NRING;
+      const bool ring = rt < NRING;
       int ri = 0, rj = 0;
-      Sym<S> ring_p = sym_zero<S>();
-      if (ring) {
-        ring_point<TX, TY>(tid, ri, rj);
+      auto pred_ring = [&]() {
+        ring_point<TX, TY>(rt, ri, rj);
         Stash tmp;
-        ring_p = pred_point(slot(p), slot(p + 1), slot(p - 1), ri, rj, tmp);
-        if constexpr (!ZREG) store_pred(pslot(p), ri, rj, ring_p);
+        return pred_point(slot(p), slot(p + 1), slot(p - 1), ri, rj, tmp);
+      };
+      if constexpr (!ZREG) {
+        store_pred(pslot(p), tx + 1, ty + 1, own_p);
+        if (ring) {
+          const Sym<S> ring_p = pred_ring();
+          store_pred(pslot(p), ri, rj, ring_p);
+        }
       }
       if constexpr (ZREG) {
-        const Sym<S> pc = qp_of(prev);  // Q^P of plane p-1
-        if (p - 1 >= zb) corr_site(p - 1, 0, prev, pc, own_p, pm);
+        // Q and u of the owner's site in plane p-1, still in slot(p-1)
+        Stash st = prev;
+        const int k = T::r2(tx + 1, ty + 1);
+        const auto& sC = sQ[slot(p - 1)];
+        st.q = Sym<S>{sC[0][k], sC[1][k], sC[2][k], sC[3][k], sC[4][k]};
+#pragma unroll
+        for (int a = 0; a < DIM; a++) st.fl.u[a] = sC[5 + a][k] * S(0.5);
+        const Sym<S> pc = qp_of(st);  // Q^P of plane p-1
+        if (p - 1 >= zb) corr_site(p - 1, 0, st, pc, own_p, pm);
+        Sym<S> ring_p = sym_zero<S>();
+        if (ring) ring_p = pred_ring();
         // every corrector has read plane p-1 of Q^P, every predictor plane
         // p-1 of Q and u: both may be overwritten
         __syncthreads();
@@ -859,8 +880,15 @@ __global__ void __launch_bounds__(TX* TY) __attribute__((amdgpu_waves_per_eu(WPE
             int zc, S* __restrict__ rec, uint32_t srkey) {
   const int nb = gridDim.x * gridDim.y * gridDim.z;
   const int t = xcd_remap(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), nb);
+  // The ring's points go to the block's first waves, and a CU deals the waves
+  // of every block to its SIMDs alike: two blocks on a CU would both have
+  // theirs on the same SIMDs.  Of up to two blocks per CU the second 256, which
+  // join the first on the 256 CUs, give them to other waves (64^3 in FP64:
+  // 22.7 -> 20.6 us; with more blocks, whose places are not known, 237 -> 243
+  // on 200x180x150, and no difference in the stress/LB sweep).
+  const bool turn = nb <= 512 && blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z) >= 256;
   split_q_body<LAT, S, TX, TY, SR, ST>(Qin, uin, Qout, g, c, zc, t % gridDim.x, (t / gridDim.x) % gridDim.y,
-                                   t / (gridDim.x * gridDim.y), rec, srkey);
+                                   t / (gridDim.x * gridDim.y), rec, srkey, turn);
 }
 
 // Tile shapes of the two-sweep kernels (measured on 256^3; LDS per block at

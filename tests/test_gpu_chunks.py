@@ -1,7 +1,8 @@
 """The default z-chunks of the 3D sweeps, which follow from the number of
 tiles: every chunk gives the same state bit for bit, so the default must equal
 one chunk over the whole depth, at depths below, at and beyond the planes a
-block marches."""
+block marches, and with a second block on every CU (the last shape), whose
+ring points other waves take."""
 import numpy as np
 import pytest
 
@@ -15,7 +16,7 @@ PARAMS = (1.0, 2.72, 0.05, 0.3, 0.7, 1.3)
 
 @pytest.mark.parametrize("precision,stencil,variant", [("fp32dev", 0, 2), ("fp64", 0, 2), ("mixed", 0, 2),
                                                        ("fp32dev", 1, 2), ("fp64", 1, 2), ("fp32dev", 0, 3)])
-@pytest.mark.parametrize("shape", [(1, 9, 33), (2, 8, 64), (17, 24, 20), (130, 9, 40)])
+@pytest.mark.parametrize("shape", [(1, 9, 33), (2, 8, 64), (17, 24, 20), (130, 9, 40), (60, 64, 64)])
 def test_default_chunk_equals_whole_depth(precision, stencil, variant, shape):
     require_gpu()
     from paper_1907_13415_amd import lc
