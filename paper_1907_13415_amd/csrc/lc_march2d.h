@@ -8,13 +8,14 @@
 // row p-3 and the corrector of row p-4 (Sec. 1.2.2).  Neighbours in x are the
 // neighbouring lanes (DPP wave shifts, an operand of the instruction that uses
 // them), neighbours in y the lane's own registers of earlier rows, so there is
-// no LDS, no barrier and no block: every stage is evaluated once per site, but
-// for the halo lanes (64 for 56) and the rows a chunk repeats (six of stress
-// down to none of the corrector).  f and Q are read once and written once.
+// no barrier and no block: every stage is evaluated once per site, but for the
+// halo lanes (64 for 56) and the rows a chunk repeats (six of stress down to
+// none of the corrector).  f and Q are read once and written once.
 //
 // The arithmetic is that of the two sweeps and of the tiled single pass, in
 // the same order (bit-identical); the gradient, Laplacian and molecular field
-// of Q that the stress needs are kept for the predictor, which needs the same.
+// of Q that the stress needs are kept (in LDS, each lane its own) for the
+// predictor, which needs the same.
 #pragma once
 
 #include "lc_split.h"

@@ -330,6 +330,20 @@ constexpr int iso_lb_tx() {
 }
 constexpr int ISO_LB_TY = 8;
 
+// Whether a sweep stores its output (values of `size` bytes) with the
+// nontemporal hint: where the grid's rows are whole 64-byte pieces and the
+// state (both buffers) is larger than the 256 MB cache in front of the memory,
+// in which it would otherwise stay for the next step.  Measured per step,
+// nontemporal and plain: 270^3 (rows of 1080 bytes) FP32 1774 and 1510 us, FP64
+// (2160 bytes) 3267 and 2854; 200x180x150 FP32 (800 bytes) 457 and 438, FP64
+// (1600 = 25 x 64 bytes) 727 and 752; 256^3 FP32 987 and 1031; 96^3 FP32 (170
+// MB) 80.6 and 73, 112^3 (270 MB) 116 and 119; 512^2 FP64 22.7 and 20.1.
+template <int LAT, typename S, typename QT>
+static bool stream_stores(const lc_grid& g, size_t size) {
+  const size_t sites = size_t(g.nx) * g.ny * g.nz;
+  return size_t(g.nx) * size % 64 == 0 && 2 * sites * (Lattice<LAT>::q * sizeof(S) + 5 * sizeof(QT)) > (size_t(256) << 20);
+}
+
 // The chunks of the context's steps: as set by lc_set_chunk, else by
 // pick_chunk (once per call, not per step).  Chunks longer than the grid are
 // the whole depth (the block index arithmetic stays within int).
@@ -361,6 +375,7 @@ static void step_split_ptrs(lc_ctx* c, hipStream_t st, bool mark, const Chunks& 
   const Coef<S> k = ctx_coef<S>(c);
   const Coef<QT> kq = ctx_coef<QT>(c);
   const int zc1 = z.lb, zc2 = z.q;
+  const bool stream_f = stream_stores<LAT, S, QT>(c->g, sizeof(S)), stream_q = stream_stores<LAT, S, QT>(c->g, sizeof(QT));
   const dim3 g1((c->g.nx + C::LB_TX - 1) / C::LB_TX, (c->g.ny + C::LB_TY - 1) / C::LB_TY,
                 unsigned((c->g.nz + zc1 - 1) / zc1));
   const dim3 g2((c->g.nx + C::Q_TX - 1) / C::Q_TX, (c->g.ny + C::Q_TY - 1) / C::Q_TY,
@@ -372,35 +387,35 @@ static void step_split_ptrs(lc_ctx* c, hipStream_t st, bool mark, const Chunks& 
       const dim3 gi((c->g.nx + ITX - 1) / ITX, (c->g.ny + ITY - 1) / ITY, unsigned((c->g.nz + zc1 - 1) / zc1));
       if (c->coll == LC_COLL_MRT)
         hipLaunchKernelGGL((split_lb<LAT, S, DEV, ITX, ITY, 1, true, QT, STENCIL_ISO>), gi, dim3(ITX, ITY), 0, st, q0,
-                           f0, f1, u, gd, k, kq, zc1, rec_lb);
+                           f0, f1, u, gd, k, kq, zc1, rec_lb, stream_f);
       else
         hipLaunchKernelGGL((split_lb<LAT, S, DEV, ITX, ITY, 1, false, QT, STENCIL_ISO>), gi, dim3(ITX, ITY), 0, st,
-                           q0, f0, f1, u, gd, k, kq, zc1, rec_lb);
+                           q0, f0, f1, u, gd, k, kq, zc1, rec_lb, stream_f);
       ctx_end(c, st, e, 0);
       e = mark ? ctx_begin(c, st) : nullptr;
       // the 3D float Q sweep with these stencils is held to two waves per
       // SIMD (some registers spill; measured 12% faster than one wave)
       constexpr int IQW = (C::d3 && sizeof(QT) == 4) ? 2 : C::Q_WPE;
       hipLaunchKernelGGL((split_q<LAT, QT, C::Q_TX, C::Q_TY, IQW, false, STENCIL_ISO>), g2,
-                         dim3(C::Q_TX, C::Q_TY), 0, st, q0, u, q1, gd, kq, zc2, rec_q, 0u);
+                         dim3(C::Q_TX, C::Q_TY), 0, st, q0, u, q1, gd, kq, zc2, rec_q, 0u, stream_q);
       ctx_end(c, st, e, 1);
       return;
     }
   }
   if (c->coll == LC_COLL_MRT)
     hipLaunchKernelGGL((split_lb<LAT, S, DEV, C::LB_TX, C::LB_TY, C::LB_WPE, true, QT>), g1,
-                       dim3(C::LB_TX, C::LB_TY), 0, st, q0, f0, f1, u, gd, k, kq, zc1, rec_lb);
+                       dim3(C::LB_TX, C::LB_TY), 0, st, q0, f0, f1, u, gd, k, kq, zc1, rec_lb, stream_f);
   else
     hipLaunchKernelGGL((split_lb<LAT, S, DEV, C::LB_TX, C::LB_TY, C::LB_WPE, false, QT>), g1,
-                       dim3(C::LB_TX, C::LB_TY), 0, st, q0, f0, f1, u, gd, k, kq, zc1, rec_lb);
+                       dim3(C::LB_TX, C::LB_TY), 0, st, q0, f0, f1, u, gd, k, kq, zc1, rec_lb, stream_f);
   ctx_end(c, st, e, 0);
   e = mark ? ctx_begin(c, st) : nullptr;
   if (std::is_same<QT, float>::value && c->g.precision == LC_FP32_SR)
     hipLaunchKernelGGL((split_q<LAT, QT, C::Q_TX, C::Q_TY, C::Q_WPE, std::is_same<QT, float>::value>), g2,
-                       dim3(C::Q_TX, C::Q_TY), 0, st, q0, u, q1, gd, kq, zc2, rec_q, step_key(c->step));
+                       dim3(C::Q_TX, C::Q_TY), 0, st, q0, u, q1, gd, kq, zc2, rec_q, step_key(c->step), stream_q);
   else
     hipLaunchKernelGGL((split_q<LAT, QT, C::Q_TX, C::Q_TY, C::Q_WPE>), g2, dim3(C::Q_TX, C::Q_TY), 0, st, q0, u, q1,
-                       gd, kq, zc2, rec_q, 0u);
+                       gd, kq, zc2, rec_q, 0u, stream_q);
   ctx_end(c, st, e, 1);
 }
 
@@ -648,16 +663,14 @@ static lc_status run_steps_split(lc_ctx* c, int64_t n) {
 // own (launches are latency bound there: 256^2 5.6 us per step in FP32
 // against 9.0 in two sweeps, 7.1 against 10.0 in FP64; 384^2 8.0 against 11.1
 // and 11.5 against 14.7), marching on large grids (march_takes); in between,
-// up to 640^2 sites, in tiles where Q is float with the compact stencils
-// (512^2 11.6 against 13.4 us), and the two sweeps elsewhere (448^2 in FP64
-// 20.2 against 20.9 us, isotropic in FP32 13.6 against 15.4).
+// up to 640^2 sites, in tiles where Q is float (512^2 12.0 against 13.3 us, with
+// the isotropic stencils 14.9 against 16.3), and the two sweeps elsewhere (448^2
+// in FP64 18.7 against 20.5 us, mixed 16.2 against 17.6).
 static int resolved_variant(const lc_ctx* c) {
   if (c->variant != LC_VARIANT_AUTO) return c->variant;
   if (c->g.lattice != LC_D2Q9) return LC_VARIANT_SPLIT;
   const bool float_q = c->g.precision == LC_FP32_DEV || c->g.precision == LC_FP32_SR;
-  if (fused2d_fits(c->g) || march_takes(1, &c->g) ||
-      (float_q && c->stencil == LC_STENCIL_COMPACT && c->L.N < MARCH_MIN_SITES))
-    return LC_VARIANT_FUSED;
+  if (fused2d_fits(c->g) || march_takes(1, &c->g) || (float_q && c->L.N < MARCH_MIN_SITES)) return LC_VARIANT_FUSED;
   return LC_VARIANT_SPLIT;
 }
 

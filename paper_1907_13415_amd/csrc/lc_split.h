@@ -319,6 +319,23 @@ __device__ __forceinline__ void store_out(S* p, S v) {
   __builtin_nontemporal_store(v, p);
 }
 
+// The NC components of site s; stream: with the nontemporal hint, which is
+// right for rows of whole 64-byte pieces.  A nontemporal store of part of one
+// reaches memory by itself, where the cache would have completed it with the
+// neighbouring block's.
+template <typename S, int NC>
+__device__ __forceinline__ void store_site(S* __restrict__ out, size_t N, uint32_t s, const S (&v)[NC], bool stream) {
+  if (stream) {
+#pragma unroll
+    for (int k = 0; k < NC; k++) store_out(&(out + size_t(k) * N)[s], v[k]);
+  } else {
+    asm volatile("");  // keeps the compiler from merging the two branches into one without the hint
+#pragma unroll
+    for (int k = 0; k < NC; k++) (out + size_t(k) * N)[s] = v[k];
+    asm volatile("");
+  }
+}
+
 // STREAM_F: read the populations with nontemporal loads (each is pulled by
 // one site only; measured to help where many grids share the caches, and to
 // hurt a single small grid that stays resident in them).  QT: the type of Q
@@ -330,7 +347,7 @@ template <int LAT, typename S, bool DEV, int TX, int TY, bool MRT = false, bool 
 __device__ __forceinline__ void split_lb_body(const QT* __restrict__ Qin, const S* __restrict__ fin,
                                               S* __restrict__ fout, QT* __restrict__ uout, const GridDims& g,
                                               const Coef<S>& c, const Coef<QT>& cq, int zc, int bx, int by, int bz,
-                                              S* __restrict__ rec = nullptr) {
+                                              S* __restrict__ rec = nullptr, bool stream = true) {
   using L = Lattice<LAT>;
   using T = Tile<TX, TY>;
   constexpr int DIM = L::dim;
@@ -542,8 +559,7 @@ __device__ __forceinline__ void split_lb_body(const QT* __restrict__ Qin, const 
       collide_mrt<LAT, S, DEV>(f, rho, mass, u, F, c);
     else
       collide_pairs<LAT, S, DEV>(f, rho, mass, u, F, c);
-#pragma unroll
-    for (int i = 0; i < L::q; i++) store_out(&(fout + size_t(i) * size_t(N))[s], f[i]);
+    store_site(fout, size_t(N), s, f, stream);
   };
 
   const RegionIdx<TX, TY> ridx(x0, y0, g, tid);
@@ -596,11 +612,12 @@ template <int LAT, typename S, bool DEV, int TX, int TY, int WPE, bool MRT = fal
           int ST = STENCIL_COMPACT>
 __global__ void __launch_bounds__(TX* TY) __attribute__((amdgpu_waves_per_eu(WPE)))
     split_lb(const QT* __restrict__ Qin, const S* __restrict__ fin, S* __restrict__ fout, QT* __restrict__ uout,
-             GridDims g, Coef<S> c, Coef<QT> cq, int zc, S* __restrict__ rec) {
+             GridDims g, Coef<S> c, Coef<QT> cq, int zc, S* __restrict__ rec, bool stream) {
   const int nb = gridDim.x * gridDim.y * gridDim.z;
   const int t = xcd_remap(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), nb);
   split_lb_body<LAT, S, DEV, TX, TY, MRT, false, QT, ST>(Qin, fin, fout, uout, g, c, cq, zc, t % gridDim.x,
-                                                     (t / gridDim.x) % gridDim.y, t / (gridDim.x * gridDim.y), rec);
+                                                     (t / gridDim.x) % gridDim.y, t / (gridDim.x * gridDim.y), rec,
+                                                     stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -612,7 +629,7 @@ template <int LAT, typename S, int TX, int TY, bool SR = false, int ST = STENCIL
 __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S* __restrict__ uin,
                                              S* __restrict__ Qout, const GridDims& g, const Coef<S>& c, int zc,
                                              int bx, int by, int bz, S* __restrict__ rec = nullptr,
-                                             uint32_t srkey = 0, bool turn = false) {
+                                             uint32_t srkey = 0, bool stream = true, bool turn = false) {
   using L = Lattice<LAT>;
   using T = Tile<TX, TY>;
   constexpr int DIM = L::dim;
@@ -726,6 +743,11 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
   };
   const int k1 = (tx + 1) + T::W1 * (ty + 1);
   auto pred_at = [&](int b) { return Sym<S>{sP[b][0][k1], sP[b][1][k1], sP[b][2][k1], sP[b][3][k1], sP[b][4][k1]}; };
+  auto store_q = [&](int64_t s, const Sym<S>& q, const Sym<S>& r, const Sym<S>& rp) {
+    S v[5];
+    q_update<S, SR>(uint32_t(s), q, r, rp, srkey, [&](int k, S w) { v[k] = w; });
+    store_site(Qout, size_t(N), uint32_t(s), v, stream);
+  };
   // corrector at the owner's site of plane z: in-plane neighbours of Q^P
   // from sP[b], the centre pc and the z neighbours pzp / pzm (3D)
   // (bzp, bzm: the predictor planes above and below, read by the isotropic
@@ -743,6 +765,8 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
       const Sym<S> Rp = be_rate_flow<S, true, DIM>(pcc, H, d, st.fl, c);
       const int64_t s = uint32_t(x) + uint32_t(g.nx) * (uint32_t(y) + uint32_t(g.ny) * uint32_t(z));
       if (rec) store_sym(rec, N, s, pcc);
+      // nontemporal for rows of any length (no difference at 250^3, and a
+      // second set of stores costs this form 5%)
       store_q_update<S, SR>(Qout, N, s, st.q, st.r, Rp, srkey);
       return;
     }
@@ -774,7 +798,7 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
     const Sym<S> Rp = be_rate_flow<S, true, DIM>(pc, H, d, st.fl, c);
     const int64_t s = uint32_t(x) + uint32_t(g.nx) * (uint32_t(y) + uint32_t(g.ny) * uint32_t(z));
     if (rec) store_sym(rec, N, s, pc);  // record the predictor (reverse-mode replay)
-    store_q_update<S, SR>(Qout, N, s, st.q, st.r, Rp, srkey);
+    store_q(s, st.q, st.r, Rp);
   };
 
   const RegionIdx<TX, TY> ridx(x0, y0, g, tid);
@@ -877,7 +901,7 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
 template <int LAT, typename S, int TX, int TY, int WPE, bool SR = false, int ST = STENCIL_COMPACT>
 __global__ void __launch_bounds__(TX* TY) __attribute__((amdgpu_waves_per_eu(WPE)))
     split_q(const S* __restrict__ Qin, const S* __restrict__ uin, S* __restrict__ Qout, GridDims g, Coef<S> c,
-            int zc, S* __restrict__ rec, uint32_t srkey) {
+            int zc, S* __restrict__ rec, uint32_t srkey, bool stream) {
   const int nb = gridDim.x * gridDim.y * gridDim.z;
   const int t = xcd_remap(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), nb);
   // The ring's points go to the block's first waves, and a CU deals the waves
@@ -888,7 +912,7 @@ __global__ void __launch_bounds__(TX* TY) __attribute__((amdgpu_waves_per_eu(WPE
   // on 200x180x150, and no difference in the stress/LB sweep).
   const bool turn = nb <= 512 && blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z) >= 256;
   split_q_body<LAT, S, TX, TY, SR, ST>(Qin, uin, Qout, g, c, zc, t % gridDim.x, (t / gridDim.x) % gridDim.y,
-                                   t / (gridDim.x * gridDim.y), rec, srkey, turn);
+                                   t / (gridDim.x * gridDim.y), rec, srkey, stream, turn);
 }
 
 // Tile shapes of the two-sweep kernels (measured on 256^3; LDS per block at
