@@ -368,11 +368,13 @@ def run_batch(torch, lc, stream, dev, steps, tiles=None, physics=True):
         sweep = batch_velocities(b, ws) if physics else None
         del b
         # the same batch in the float form with stochastic rounding, on the
-        # tile shapes just chosen
+        # launch shapes it is fastest with
         bs = lc.BatchSolver("fp32sr", shapes, [w.params for w in ws], device=dev, stream=stream)
         for k, w in enumerate(ws):
             bs.load(k, w.q5)
-        bs.set_tiles(tile % 7, tile // 7)
+        bs.autotune(10)
+        for k, w in enumerate(ws):
+            bs.load(k, w.q5)
         bs.step(64)
         torch.cuda.synchronize()
         t0.record(stream)
