@@ -17,25 +17,9 @@
 #pragma once
 
 #include "lc_fused.h"
+#include "lc_launch.h"
 
 namespace lc {
-
-// Shapes of the single pass on two-dimensional grids: tiles of TX x TY
-// sites, all with 1024 threads.  A step of a small grid is a chain of stages
-// with a barrier between them, and a CU that holds one block spends the chain
-// once; so the runtime takes the smallest tile with which the grid has at
-// most one tile per CU (16x8 up to 32x20, whose radius-3 rectangle of 38x26
-// points still has one thread per point).  Measured per step in the mixed
-// form on 301x419 sites: 15.4 us with 530 tiles of 32x8 sites and 512 threads
-// (two rounds of blocks), 9.7 us with 210 tiles of 32x20; on 256^2 sites (32x8
-// tiles) 7.4 -> 7.1 us in FP64 and 5.9 -> 5.6 us in FP32, on 128x16 (16x8)
-// 6.0 -> 4.9 us in FP64, against the same tiles without the overlap above.
-constexpr int FUSED2D_NTHR = 1024;
-constexpr int FUSED2D_CUS = 256;  // compute units of the chip
-constexpr int FUSED2D_PAIR_TX = 16, FUSED2D_PAIR_TY = 8;  // tiles of two steps per launch
-constexpr int FUSED2D_NV = 5;
-__host__ __device__ constexpr int fused2d_tx(int v) { return v == 0 ? 16 : 32; }
-__host__ __device__ constexpr int fused2d_ty(int v) { return v < 2 ? 8 : (v == 2 ? 12 : (v == 3 ? 16 : 20)); }
 
 // Rectangles of a tile and the LDS its stages take (values of the order-tensor
 // type): Q on radius 4, the stress, the velocity on radius 2, Q^P on radius 1.

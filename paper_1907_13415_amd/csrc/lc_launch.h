@@ -1,0 +1,156 @@
+// lc_launch.h -- which kernel and launch shape a grid takes: the rules of the
+// dispatch, on sizes and element sizes alone.  Host arithmetic in plain C++.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "../../include/lc.h"
+
+namespace lc {
+
+constexpr int NUM_CU = 256;  // compute units of the chip
+
+// Planes per block along z for a sweep of `tiles` column tiles on a grid of
+// nz planes, at most `most`.  A block of zc planes marches zc + `extra`
+// planes, one after another, so a grid with few tiles is bound by that serial
+// chain while most CUs idle: there shorter chunks win in spite of the planes
+// they compute twice.  The estimate counts, per CU, the marches that run one
+// after another; a march that shares its CU with one other takes 1.4 times as
+// long as alone (measured 1.3-1.6), with two others 1.85 times (Q sweep,
+// 1.8-1.9).
+// Measured on the stress/LB and Q sweeps, long default chunks against the
+// chosen ones: 24^3 FP32 67.7 -> 14.7 and 56.9 -> 11.7 us, 64^3 FP64
+// 80 -> 32 and 147 -> 24 us, 129x100x75 FP32 isotropic 186 -> 95 and
+// 474 -> 111 us; from 256^3 on the chunk is the longest allowed.
+inline int pick_chunk(int nz, int64_t tiles, int most, int extra, int resident = 2) {
+  constexpr double BESIDE[4] = {0.0, 1.0, 1.4, 1.85};  // by blocks on the CU
+  int best = 1;
+  double best_cost = 1e300;
+  for (int zc = 1; zc <= std::min(most, nz); zc++) {
+    const int64_t blocks = tiles * ((nz + zc - 1) / zc);
+    const int64_t full = blocks / (NUM_CU * resident), rest = blocks % (NUM_CU * resident);
+    const double rounds = double(full) * BESIDE[resident] + BESIDE[(rest + NUM_CU - 1) / NUM_CU];
+    const double cost = rounds * (zc + extra);
+    if (cost <= best_cost) {
+      best_cost = cost;
+      best = zc;
+    }
+  }
+  return best;
+}
+
+// Shapes of the single pass on two-dimensional grids (lc_fused2d.h): tiles of
+// TX x TY sites, all with 1024 threads.  A step of a small grid is a chain of
+// stages with a barrier between them, and a CU that holds one block spends the
+// chain once; so a grid takes the smallest tile with which it has at most one
+// tile per CU (16x8 up to 32x20, whose radius-3 rectangle of 38x26 points still
+// has one thread per point).  Measured per step in the mixed form on 301x419
+// sites: 15.4 us with 530 tiles of 32x8 sites and 512 threads (two rounds of
+// blocks), 9.7 us with 210 tiles of 32x20; on 256^2 sites (32x8 tiles)
+// 7.4 -> 7.1 us in FP64 and 5.9 -> 5.6 us in FP32, on 128x16 (16x8) 6.0 -> 4.9
+// us in FP64, against the same tiles without the overlap of their stages.
+constexpr int FUSED2D_NTHR = 1024;
+constexpr int FUSED2D_PAIR_TX = 16, FUSED2D_PAIR_TY = 8;  // tiles of two steps per launch
+constexpr int FUSED2D_NV = 5;
+constexpr int fused2d_tx(int v) { return v == 0 ? 16 : 32; }
+constexpr int fused2d_ty(int v) { return v < 2 ? 8 : (v == 2 ? 12 : (v == 3 ? 16 : 20)); }
+
+inline int64_t fused2d_tiles(const lc_grid& g, int v) {
+  return int64_t((g.nx + fused2d_tx(v) - 1) / fused2d_tx(v)) * ((g.ny + fused2d_ty(v) - 1) / fused2d_ty(v));
+}
+inline int fused2d_shape(const lc_grid& g) {
+  for (int v = 0; v < FUSED2D_NV; v++)
+    if (fused2d_tiles(g, v) <= NUM_CU) return v;
+  return FUSED2D_NV - 1;
+}
+inline bool fused2d_fits(const lc_grid& g) { return fused2d_tiles(g, FUSED2D_NV - 1) <= NUM_CU; }
+
+// The marching single pass (lc_march2d.h): columns of a strip.
+constexpr int MARCH_HALO = 4, MARCH_COLS = 64 - 2 * MARCH_HALO;
+
+inline int64_t march_strips(const lc_grid& g) { return (g.nx + MARCH_COLS - 1) / MARCH_COLS; }
+
+// Waves of the march that the chip holds at once: two per SIMD where Q is
+// float, one where it is double (the registers set it).  Chunks are cut so
+// that a launch has at most that many, in one round; measured per step on
+// 2048^2 sites, FP32: 130 us with 1998 waves of 38 rows, 160 with 2368 waves
+// of 32 rows (a second round for the rest), 178 with 814 waves of 96 rows.
+constexpr int march_waves(bool double_q) { return (double_q ? 4 : 8) * NUM_CU; }
+inline bool double_q(const lc_grid& g) { return g.precision == LC_FP64 || g.precision == LC_MIXED; }
+
+// Rows per chunk of the marching single pass for n grids of one precision
+// together: the fewest whose waves are on the chip at once (all, where the
+// strips alone are more).
+inline int march_rows(int n, const lc_grid* g) {
+  auto waves = [&](int64_t rows) {
+    int64_t w = 0;
+    for (int k = 0; k < n; k++) w += march_strips(g[k]) * ((g[k].ny + rows - 1) / rows);
+    return w;
+  };
+  int most = 1;
+  for (int k = 0; k < n; k++) most = std::max(most, int(g[k].ny));
+  int lo = 1, hi = most;  // waves() falls with the rows
+  while (lo < hi) {
+    const int mid = lo + (hi - lo) / 2;
+    if (waves(mid) <= march_waves(double_q(g[0])))
+      hi = mid;
+    else
+      lo = mid + 1;
+  }
+  return lo;
+}
+
+// Whether the marching single pass takes n 2D grids (one, or the grids of a
+// batch) of at least MARCH_MIN_SITES sites together.  Below that its waves
+// have too few rows each to be worth the eight they repeat: 512^2 in FP32
+// 15.0 us per step against 11.6 in tiles and 13.4 in two sweeps, in FP64 24.1
+// against 21.7 and 22.8; 700^2 20.0 against 24.7 in two sweeps, and 32.7
+// against 38.9; 1400^2 46.6 against 80.7, and 125 against 150.  A strip is 56
+// columns wide: grids that fill less than three quarters of their strips stay
+// in tiles, and so do components beyond 32-bit byte offsets.
+constexpr int64_t MARCH_MIN_SITES = 640 * 640;
+inline bool march_offsets_fit(int n, const lc_grid* g) {
+  for (int k = 0; k < n; k++)
+    if (int64_t(g[k].nx) * g[k].ny > (int64_t(1) << 32) / 8) return false;
+  return true;
+}
+inline bool march_takes(int n, const lc_grid* g) {
+  if (!march_offsets_fit(n, g)) return false;
+  int64_t sites = 0, lanes = 0;
+  for (int k = 0; k < n; k++) {
+    sites += int64_t(g[k].nx) * g[k].ny;
+    lanes += march_strips(g[k]) * MARCH_COLS * g[k].ny;
+  }
+  return sites >= MARCH_MIN_SITES && 4 * sites >= 3 * lanes;
+}
+
+// The form of a step of a two-dimensional grid in the single pass.
+enum Form2d { FORM_TILES, FORM_PAIRS, FORM_STRIPS };
+inline Form2d fused2d_form(const lc_grid& g, bool isotropic, bool timed) {
+  if (march_takes(1, &g)) return FORM_STRIPS;
+  // two steps go in a launch where every 16x8 tile has a CU; not where
+  // launches are timed one by one, nor in FP64 with the isotropic stencils,
+  // whose larger first step spills (64^2 6.6 us per step in pairs against 6.2)
+  if (fused2d_shape(g) == 0 && !timed && !(g.precision == LC_FP64 && isotropic)) return FORM_PAIRS;
+  return FORM_TILES;
+}
+
+// The variant AUTO runs (bit-identical results).  The two sweeps in 3D.  In 2D
+// the single pass, in tiles where each has a CU of its own (launches are
+// latency bound there: 256^2 5.6 us per step in FP32 against 9.0 in two sweeps,
+// 7.1 against 10.0 in FP64; 384^2 8.0 against 11.1 and 11.5 against 14.7),
+// marching on large grids (march_takes); in between, up to 640^2 sites, in
+// tiles where Q is float (512^2 12.0 against 13.3 us, with the isotropic
+// stencils 14.9 against 16.3), and the two sweeps elsewhere (448^2 in FP64
+// 18.7 against 20.5 us, mixed 16.2 against 17.6).
+inline int auto_variant(const lc_grid& g) {
+  if (g.lattice != LC_D2Q9) return LC_VARIANT_SPLIT;
+  if (fused2d_fits(g) || march_takes(1, &g) || (!double_q(g) && int64_t(g.nx) * g.ny < MARCH_MIN_SITES))
+    return LC_VARIANT_FUSED;
+  return LC_VARIANT_SPLIT;
+}
+
+}  // namespace lc

@@ -18,11 +18,10 @@
 // predictor, which needs the same.
 #pragma once
 
+#include "lc_launch.h"
 #include "lc_split.h"
 
 namespace lc {
-
-constexpr int MARCH_HALO = 4, MARCH_COLS = 64 - 2 * MARCH_HALO;
 
 // Value of the lane to the right (D = 1) or left (D = -1); zero beyond the wave.
 template <int D>
@@ -318,16 +317,6 @@ __device__ __forceinline__ void march2d_body(const QT* __restrict__ Qin, const S
     if (p + 1 <= ye + 3) iteration(std::integral_constant<int, 1>{}, p + 1);
     if (p + 2 <= ye + 3) iteration(std::integral_constant<int, 2>{}, p + 2);
   }
-}
-
-// Waves of the march that the chip holds at once: two per SIMD where Q is
-// float, one where it is double (the registers set it).  Chunks are cut so
-// that a launch has at most that many, in one round; measured per step on
-// 2048^2 sites, FP32: 130 us with 1998 waves of 38 rows, 160 with 2368 waves
-// of 32 rows (a second round for the rest), 178 with 814 waves of 96 rows.
-template <typename QT>
-constexpr int march_waves() {
-  return sizeof(QT) == 4 ? 2048 : 1024;
 }
 
 template <typename S, bool DEV, bool MRT, typename QT, bool SR, int ST = STENCIL_COMPACT>

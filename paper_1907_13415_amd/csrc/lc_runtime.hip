@@ -1,5 +1,5 @@
 // lc_runtime.hip -- the C ABI of include/lc.h: validation, context, scratch
-// layout, kernel dispatch over (lattice, precision, variant).
+// layout, kernel dispatch over (lattice, precision, variant) by the rules of lc_launch.h.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "../../include/lc.h"
+#include "lc_launch.h"
 #include "lc_aux.h"
 #include "lc_split.h"
 #include "lc_fused.h"
@@ -285,37 +286,6 @@ static lc_status run_steps_staged(lc_ctx* c, int64_t n) {
   }
 }
 
-
-// Planes per block along z for a sweep of `tiles` column tiles on a grid of
-// nz planes, at most `most`.  A block of zc planes marches zc + `extra`
-// planes, one after another, so a grid with few tiles is bound by that serial
-// chain while most CUs idle: there shorter chunks win in spite of the planes
-// they compute twice.  The estimate counts, per CU, the marches that run one
-// after another; a march that shares its CU with one other takes 1.4 times as
-// long as alone (measured 1.3-1.6), with two others 1.85 times (Q sweep,
-// 1.8-1.9).
-// Measured on the stress/LB and Q sweeps, long default chunks against the
-// chosen ones: 24^3 FP32 67.7 -> 14.7 and 56.9 -> 11.7 us, 64^3 FP64
-// 80 -> 32 and 147 -> 24 us, 129x100x75 FP32 isotropic 186 -> 95 and
-// 474 -> 111 us; from 256^3 on the chunk is the longest allowed.
-static int pick_chunk(int nz, int64_t tiles, int most, int extra, int resident = 2) {
-  constexpr int CUS = 256;
-  constexpr double BESIDE[4] = {0.0, 1.0, 1.4, 1.85};  // by blocks on the CU
-  int best = 1;
-  double best_cost = 1e300;
-  for (int zc = 1; zc <= std::min(most, nz); zc++) {
-    const int64_t blocks = tiles * ((nz + zc - 1) / zc);
-    const int64_t full = blocks / (CUS * resident), rest = blocks % (CUS * resident);
-    const double rounds = double(full) * BESIDE[resident] + BESIDE[(rest + CUS - 1) / CUS];
-    const double cost = rounds * (zc + extra);
-    if (cost <= best_cost) {
-      best_cost = cost;
-      best = zc;
-    }
-  }
-  return best;
-}
-
 // Chunks of the two sweeps (planes per block along z).
 struct Chunks {
   int lb, q;
@@ -459,71 +429,12 @@ static void launch_fused2d_rec(lc_ctx* c, hipStream_t st, const double* f0, cons
                      dim3(FUSED2D_NTHR), 0, st, q0, f0, f1, q1, gd, k, k, 0u, rec);
 }
 
-// The tile shape of the single pass on a 2D grid: the smallest with which
-// every tile has a CU of its own, else the largest (lc_fused2d.h).
-static int64_t fused2d_tiles(const lc_grid& g, int v) {
-  return int64_t((g.nx + fused2d_tx(v) - 1) / fused2d_tx(v)) * ((g.ny + fused2d_ty(v) - 1) / fused2d_ty(v));
-}
-static int fused2d_shape(const lc_grid& g) {
-  for (int v = 0; v < FUSED2D_NV; v++)
-    if (fused2d_tiles(g, v) <= FUSED2D_CUS) return v;
-  return FUSED2D_NV - 1;
-}
-static bool fused2d_fits(const lc_grid& g) { return fused2d_tiles(g, FUSED2D_NV - 1) <= FUSED2D_CUS; }
-
-// Rows per chunk of the marching single pass (lc_march2d.h) for grids of
-// nx[k] * ny[k] sites together: the fewest whose waves are on the chip at
-// once.
-template <typename QT>
-static int march_rows(int n, const lc_grid* g) {
-  auto waves = [&](int64_t rows) {
-    int64_t w = 0;
-    for (int k = 0; k < n; k++) w += int64_t((g[k].nx + MARCH_COLS - 1) / MARCH_COLS) * ((g[k].ny + rows - 1) / rows);
-    return w;
-  };
-  int most = 1;
-  for (int k = 0; k < n; k++) most = std::max(most, g[k].ny);
-  int lo = 1, hi = most;  // waves() falls with the rows
-  while (lo < hi) {
-    const int mid = lo + (hi - lo) / 2;
-    if (waves(mid) <= march_waves<QT>())
-      hi = mid;
-    else
-      lo = mid + 1;
-  }
-  return lo;
-}
-
-// Whether the marching single pass takes n 2D grids (one, or the grids of a
-// batch) of at least MARCH_MIN_SITES sites together.  Below that its waves
-// have too few rows each to be worth the eight they repeat: 512^2 in FP32
-// 15.0 us per step against 11.6 in tiles and 13.4 in two sweeps, in FP64 24.1
-// against 21.7 and 22.8; 700^2 20.0 against 24.7 in two sweeps, and 32.7
-// against 38.9; 1400^2 46.6 against 80.7, and 125 against 150.  A strip is 56
-// columns wide: grids that fill less than three quarters of their strips stay
-// in tiles, and so do components beyond 32-bit byte offsets.
-constexpr int64_t MARCH_MIN_SITES = 640 * 640;
-static bool march_offsets_fit(int n, const lc_grid* g) {
-  for (int k = 0; k < n; k++)
-    if (int64_t(g[k].nx) * g[k].ny > (int64_t(1) << 32) / 8) return false;
-  return true;
-}
-static bool march_takes(int n, const lc_grid* g) {
-  if (!march_offsets_fit(n, g)) return false;
-  int64_t sites = 0, lanes = 0;
-  for (int k = 0; k < n; k++) {
-    sites += int64_t(g[k].nx) * g[k].ny;
-    lanes += int64_t((g[k].nx + MARCH_COLS - 1) / MARCH_COLS) * MARCH_COLS * g[k].ny;
-  }
-  return sites >= MARCH_MIN_SITES && 4 * sites >= 3 * lanes;
-}
-
 // One launch of the marching single pass.
 template <typename S, bool DEV, typename QT, bool MRT, bool SR>
 static void launch_march2d(lc_ctx* c, hipStream_t st, const S* f0, const QT* q0, S* f1, QT* q1) {
   const GridDims gd{c->g.nx, c->g.ny, 1, c->L.N};
-  const int rows = march_rows<QT>(1, &c->g);
-  const int cols = (c->g.nx + MARCH_COLS - 1) / MARCH_COLS;
+  const int rows = march_rows(1, &c->g);
+  const int cols = int(march_strips(c->g));
   const dim3 grid(unsigned(cols) * unsigned((c->g.ny + rows - 1) / rows));
   if constexpr (std::is_same<S, QT>::value && !SR) {
     if (c->stencil == LC_STENCIL_ISOTROPIC) {
@@ -545,7 +456,7 @@ static void step_fused_form(lc_ctx* c, hipStream_t st, const S* f0, const QT* q0
     const int zc = c->zchunk > 0 ? std::min(c->zchunk, c->g.nz) : pick_chunk(c->g.nz, tiles, C::ZC, 8, 1);
     launch_fused3d<S, DEV, QT, MRT, SR>(c, st, zc, f0, q0, f1, q1);
   } else {
-    if (march_takes(1, &c->g)) {
+    if (fused2d_form(c->g, c->stencil == LC_STENCIL_ISOTROPIC, c->timing) == FORM_STRIPS) {
       launch_march2d<S, DEV, QT, MRT, SR>(c, st, f0, q0, f1, q1);
       return;
     }
@@ -598,19 +509,15 @@ static void launch_fused2d_pair(lc_ctx* c, const S* f0, const QT* q0, S* f1, QT*
                      k, kq, step_key(c->step), step_key(c->step + 1));
 }
 
-// Steps of the single pass.  On 2D grids of at most one 16x8 tile per CU two
-// steps go in a launch, two launches at a time, so that the state after n
-// steps is in the buffers that n single steps would leave it in; launches that
-// are timed one by one are single steps, and so are those of FP64 with the
-// isotropic stencils, whose larger first step spills (64^2 6.6 us per step in
-// pairs against 6.2).
+// Steps of the single pass.  Where two steps go in a launch (fused2d_form), two
+// launches go at a time, so that the state after n steps is in the buffers that
+// n single steps would leave it in.
 template <int LAT, typename S, bool DEV, typename QT = S>
 static lc_status run_steps_fused(lc_ctx* c, int64_t n) {
   constexpr bool F32 = std::is_same<QT, float>::value;
   const bool sr = F32 && c->g.precision == LC_FP32_SR, mrt = c->coll == LC_COLL_MRT;
   if constexpr (Lattice<LAT>::dim == 2) {
-    const bool spills = sizeof(S) == 8 && c->stencil == LC_STENCIL_ISOTROPIC;
-    if (!c->timing && !spills && fused2d_shape(c->g) == 0) {
+    if (fused2d_form(c->g, c->stencil == LC_STENCIL_ISOTROPIC, c->timing) == FORM_PAIRS) {
       for (; n >= 4; n -= 4)
         for (int half = 0; half < 2; half++) {
           const S* f0 = static_cast<const S*>(c->b.f[c->parity]);
@@ -658,25 +565,9 @@ static lc_status run_steps_split(lc_ctx* c, int64_t n) {
   return hip_check(hipGetLastError(), "step launch");
 }
 
-// The variant a step runs (bit-identical results).  AUTO takes the two sweeps
-// in 3D.  In 2D it takes the single pass, in tiles where each has a CU of its
-// own (launches are latency bound there: 256^2 5.6 us per step in FP32
-// against 9.0 in two sweeps, 7.1 against 10.0 in FP64; 384^2 8.0 against 11.1
-// and 11.5 against 14.7), marching on large grids (march_takes); in between,
-// up to 640^2 sites, in tiles where Q is float (512^2 12.0 against 13.3 us, with
-// the isotropic stencils 14.9 against 16.3), and the two sweeps elsewhere (448^2
-// in FP64 18.7 against 20.5 us, mixed 16.2 against 17.6).
-static int resolved_variant(const lc_ctx* c) {
-  if (c->variant != LC_VARIANT_AUTO) return c->variant;
-  if (c->g.lattice != LC_D2Q9) return LC_VARIANT_SPLIT;
-  const bool float_q = c->g.precision == LC_FP32_DEV || c->g.precision == LC_FP32_SR;
-  if (fused2d_fits(c->g) || march_takes(1, &c->g) || (float_q && c->L.N < MARCH_MIN_SITES)) return LC_VARIANT_FUSED;
-  return LC_VARIANT_SPLIT;
-}
-
 template <int LAT, typename S, bool DEV, typename QT = S>
 static lc_status run_steps(lc_ctx* c, int64_t n) {
-  const int v = resolved_variant(c);
+  const int v = c->variant == LC_VARIANT_AUTO ? auto_variant(c->g) : c->variant;
   if (c->stencil == LC_STENCIL_ISOTROPIC && v == LC_VARIANT_FUSED && c->g.lattice != LC_D2Q9)
     return fail(LC_EUNSUPPORTED, "the single pass takes the isotropic stencils on D2Q9 grids only");
   if (v == LC_VARIANT_SPLIT) return run_steps_split<LAT, S, DEV, QT>(c, n);
@@ -1468,11 +1359,11 @@ static lc_status batch_layout_of(int32_t n, const lc_grid* grids, BatchLayout& B
   B.march_cols.assign(n, 1);
   B.march_rows.assign(n, 1);
   if (march_offsets_fit(n, grids)) {
-    const int rows = es_q == 8 ? march_rows<double>(n, grids) : march_rows<float>(n, grids);
+    const int rows = march_rows(n, grids);
     for (int k = 0; k < n; k++) {
       const int chunks = (grids[k].ny + rows - 1) / rows;
       B.march0[k] = B.march_tiles;
-      B.march_cols[k] = (grids[k].nx + MARCH_COLS - 1) / MARCH_COLS;
+      B.march_cols[k] = int(march_strips(grids[k]));
       B.march_rows[k] = (grids[k].ny + chunks - 1) / chunks;
       B.march_tiles += B.march_cols[k] * ((grids[k].ny + B.march_rows[k] - 1) / B.march_rows[k]);
     }

@@ -21,6 +21,7 @@
 // rings for the neighbours in the planes above and below.
 #pragma once
 
+#include "lc_launch.h"
 #include "lc_staged.h"
 
 namespace lc {
@@ -910,7 +911,7 @@ __global__ void __launch_bounds__(TX* TY) __attribute__((amdgpu_waves_per_eu(WPE
   // join the first on the 256 CUs, give them to other waves (64^3 in FP64:
   // 22.7 -> 20.6 us; with more blocks, whose places are not known, 237 -> 243
   // on 200x180x150, and no difference in the stress/LB sweep).
-  const bool turn = nb <= 512 && blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z) >= 256;
+  const bool turn = nb <= 2 * NUM_CU && blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z) >= NUM_CU;
   split_q_body<LAT, S, TX, TY, SR, ST>(Qin, uin, Qout, g, c, zc, t % gridDim.x, (t / gridDim.x) % gridDim.y,
                                    t / (gridDim.x * gridDim.y), rec, srkey, stream, turn);
 }

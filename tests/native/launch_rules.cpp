@@ -1,0 +1,14 @@
+// The dispatch rules of lc_launch.h as C functions, for tests/test_launch_rules.py.
+#include "../../paper_1907_13415_amd/csrc/lc_launch.h"
+
+using namespace lc;
+
+extern "C" {
+int rule_num_cu() { return NUM_CU; }
+int rule_auto_variant(const lc_grid* g) { return auto_variant(*g); }
+int rule_form2d(const lc_grid* g, int isotropic, int timed) { return fused2d_form(*g, isotropic != 0, timed != 0); }
+int rule_shape2d(const lc_grid* g) { return fused2d_shape(*g); }
+int64_t rule_tiles2d(const lc_grid* g, int v) { return fused2d_tiles(*g, v); }
+int rule_march_takes(int n, const lc_grid* g) { return march_takes(n, g); }
+int rule_march_rows(int n, const lc_grid* g) { return march_rows(n, g); }
+}

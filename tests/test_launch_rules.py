@@ -1,0 +1,78 @@
+"""CPU checks of the rules that choose a grid's kernel and launch shape
+(lc_launch.h, compiled for the host): every form gives the same values bit for
+bit, so the GPU tests that compare forms rest on these to know which ones ran."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+import test_gpu_fused2d
+from paper_1907_13415_amd import lc
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+TILES, PAIRS, STRIPS = range(3)
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("rules") / "rules.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", os.path.join(ROOT, "tests", "native", "launch_rules.cpp"),
+                    "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    lib.rule_tiles2d.restype = ctypes.c_int64
+    return lib
+
+
+def grid2d(nx, ny, precision="fp32dev"):
+    return lc.make_grid(lc.LC_D2Q9, lc.PRECISIONS[precision], nx, ny, 1)
+
+
+def ref(g):
+    return ctypes.byref(g)
+
+
+def test_forms_of_the_compared_grids(rules):
+    """The grids that the GPU test compares cover pairs, every shape of tile
+    with one tile per CU, more tiles than CUs, and strips."""
+    seen = set()
+    for nx, ny in test_gpu_fused2d.SHAPES:
+        g = grid2d(nx, ny)
+        form, shape = rules.rule_form2d(ref(g), 0, 0), rules.rule_shape2d(ref(g))
+        fits = rules.rule_tiles2d(ref(g), 4) <= rules.rule_num_cu()
+        seen.add((form, shape if form == TILES and fits else None))
+    assert seen == {(PAIRS, None), (TILES, 1), (TILES, 2), (TILES, 3), (TILES, 4), (TILES, None), (STRIPS, None)}
+
+
+@pytest.mark.parametrize("nx,ny,form", [(256, 128, PAIRS), (257, 128, TILES), (640, 640, STRIPS), (640, 639, TILES),
+                                        (64, 6400, TILES), (74, 12000, TILES), (112, 4000, STRIPS), (616, 664, TILES),
+                                        (616, 665, STRIPS)])
+def test_form_at_its_thresholds(rules, nx, ny, form):
+    """256 and 257 tiles of 16x8; 640^2 sites; strips filled to less than three
+    quarters (64 of 112 columns) and more (74 of 112 not, 112 of 112)."""
+    assert rules.rule_form2d(ref(grid2d(nx, ny)), 0, 0) == form
+
+
+def test_steps_that_are_not_paired(rules):
+    g, d = grid2d(64, 64), grid2d(64, 64, "fp64")
+    assert [rules.rule_form2d(ref(g), i, t) for i, t in ((0, 0), (1, 0), (0, 1))] == [PAIRS, PAIRS, TILES]
+    assert [rules.rule_form2d(ref(d), i, t) for i, t in ((0, 0), (1, 0), (0, 1))] == [PAIRS, TILES, TILES]
+
+
+@pytest.mark.parametrize("precision,nx,ny,variant", [
+    ("fp64", 400, 380, lc.LC_VARIANT_FUSED), ("fp64", 448, 448, lc.LC_VARIANT_SPLIT),
+    ("mixed", 448, 448, lc.LC_VARIANT_SPLIT), ("fp32dev", 448, 448, lc.LC_VARIANT_FUSED),
+    ("fp32sr", 639, 640, lc.LC_VARIANT_FUSED), ("fp64", 640, 640, lc.LC_VARIANT_FUSED),
+    ("fp64", 639, 640, lc.LC_VARIANT_SPLIT), ("fp32dev", 64, 7000, lc.LC_VARIANT_SPLIT)])
+def test_auto_variant_at_its_thresholds(rules, precision, nx, ny, variant):
+    assert rules.rule_auto_variant(ref(grid2d(nx, ny, precision))) == variant
+
+
+def test_batch_of_the_strip_test_marches(rules):
+    """The batch that the GPU test compares with two sweeps is one that
+    marches by default, and the small one of the other batch tests is not."""
+    big = [(400, 500), (333, 301), (64, 70), (600, 56), (57, 9), (300, 350)]
+    small = [(23, 37), (64, 64), (40, 96), (16, 16), (70, 130)]
+    for shapes, takes in ((big, 1), (small, 0)):
+        arr = (lc.lc_grid * len(shapes))(*[grid2d(nx, ny) for ny, nx in shapes])
+        assert rules.rule_march_takes(len(shapes), arr) == takes
