@@ -242,7 +242,7 @@ __device__ __forceinline__ void collide2d(S (&f)[9], S rho, S mass, const S (&u)
 template <int TX, int TY, bool ISO, typename S, typename QT>
 __device__ __forceinline__ void fused2d_load(const QT* __restrict__ Qin, const S* __restrict__ fin, QT* mQ,
                                              const typename Fused2d<TX, TY, ISO>::Moment& m, S (&f)[9],
-                                             const GridDims& g, int x0, int y0) {
+                                             const TileDims& g, int x0, int y0) {
   using L = Lattice<0>;
   using C = Fused2d<TX, TY, ISO>;
   using R4 = typename C::R4;
@@ -307,7 +307,7 @@ template <typename S, bool DEV, bool MRT, typename QT, bool SR, bool REC>
 struct Fused2dOut {
   S* fout;
   QT* Qout;
-  const GridDims& g;
+  const TileDims& g;
   const Coef<S>& c;
   int x0, y0;
   uint32_t srkey;
@@ -346,12 +346,12 @@ template <typename S, bool DEV, int TX, int TY, bool MRT, typename QT, bool SR, 
           bool REC = false>
 __global__ void __launch_bounds__(FUSED2D_NTHR)
     fused2d_step(const QT* __restrict__ Qin, const S* __restrict__ fin, S* __restrict__ fout, QT* __restrict__ Qout,
-                 GridDims g, Coef<S> c, Coef<QT> cq, uint32_t srkey, StepRecord rec) {
+                 TileDims g, Coef<S> c, Coef<QT> cq, uint32_t srkey, StepRecord rec) {
   constexpr bool ISO = ST == STENCIL_ISO;
   using C = Fused2d<TX, TY, ISO>;
   __shared__ QT mQ[C::NQ], mT[C::NTAU], mU[C::NU], mP[C::NP];
   const int t = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
-  const int x0 = (t % gridDim.x) * TX, y0 = (t / gridDim.x) * TY;
+  const int x0 = g.xb + (t % gridDim.x) * TX, y0 = (t / gridDim.x) * TY;
   const typename C::Moment m;
   S f[9];
   fused2d_load<TX, TY, ISO>(Qin, fin, mQ, m, f, g, x0, y0);
@@ -372,7 +372,7 @@ __global__ void __launch_bounds__(FUSED2D_NTHR)
 template <typename S, bool DEV, bool MRT, typename QT, bool SR, int ST = STENCIL_COMPACT>
 __global__ void __launch_bounds__(FUSED2D_NTHR)
     fused2d_pair(const QT* __restrict__ Qin, const S* __restrict__ fin, S* __restrict__ fout, QT* __restrict__ Qout,
-                 GridDims g, Coef<S> c, Coef<QT> cq, uint32_t srkey0, uint32_t srkey1) {
+                 TileDims g, Coef<S> c, Coef<QT> cq, uint32_t srkey0, uint32_t srkey1) {
   using L = Lattice<0>;
   constexpr int TX = FUSED2D_PAIR_TX, TY = FUSED2D_PAIR_TY, EX = TX + 8, EY = TY + 8;
   constexpr bool ISO = ST == STENCIL_ISO;

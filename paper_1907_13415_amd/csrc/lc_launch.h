@@ -13,6 +13,26 @@ namespace lc {
 
 constexpr int NUM_CU = 256;  // compute units of the chip
 
+// A two-dimensional grid of N sites as a launch with one block per tile sees
+// it: the tiles of the columns from xb on.
+struct TileDims {
+  int nx, ny, xb;
+  int64_t N;
+};
+
+// launch(blocks_x, blocks_y, xb, before) for the launches that take the tiles of
+// tx x ty sites of a two-dimensional grid, `threads` threads each: the columns
+// from xb on, after `before` blocks.  One launch, but where its threads along x
+// do not fit the runtime's 32 bits (1024 per tile of 32 columns: from 2^27
+// columns on), where several take a range of columns each.
+template <typename LAUNCH>
+inline void tile_launches(const lc_grid& g, int tx, int ty, int threads, LAUNCH launch) {
+  const int64_t most = ((int64_t(1) << 32) - 1) / threads;
+  const int64_t ntx = (int64_t(g.nx) + tx - 1) / tx, nty = (g.ny + ty - 1) / ty;
+  for (int64_t t = 0; t < ntx; t += most)
+    launch(unsigned(std::min(most, ntx - t)), unsigned(nty), int(t * tx), t * nty);
+}
+
 // Planes per block along z for a sweep of `tiles` column tiles on a grid of
 // nz planes, at most `most`.  A block of zc planes marches zc + `extra`
 // planes, one after another, so a grid with few tiles is bound by that serial

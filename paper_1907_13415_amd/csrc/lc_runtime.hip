@@ -399,22 +399,24 @@ static void launch_fused3d(lc_ctx* c, hipStream_t st, int zc, const S* f0, const
                      q1, gd, ctx_coef<S>(c), ctx_coef<QT>(c), zc, step_key(c->step));
 }
 
-// One launch of the single pass in 2D with tile shape V; the isotropic
+// The single pass in 2D with tile shape V; the isotropic
 // stencils are provided in FP64 and the FP32 deviation form (lc_set_stencil).
 template <typename S, bool DEV, typename QT, bool MRT, bool SR, int V>
 static void launch_fused2d(lc_ctx* c, hipStream_t st, const S* f0, const QT* q0, S* f1, QT* q1) {
   constexpr int TX = fused2d_tx(V), TY = fused2d_ty(V);
-  const GridDims gd{c->g.nx, c->g.ny, 1, c->L.N};
-  const dim3 grid((c->g.nx + TX - 1) / TX, (c->g.ny + TY - 1) / TY);
-  if constexpr (std::is_same<S, QT>::value && !SR) {
-    if (c->stencil == LC_STENCIL_ISOTROPIC) {
-      hipLaunchKernelGGL((fused2d_step<S, DEV, TX, TY, MRT, QT, false, STENCIL_ISO>), grid, dim3(FUSED2D_NTHR), 0, st,
-                         q0, f0, f1, q1, gd, ctx_coef<S>(c), ctx_coef<QT>(c), 0u, StepRecord{});
-      return;
+  tile_launches(c->g, TX, TY, FUSED2D_NTHR, [&](unsigned bx, unsigned by, int xb, int64_t) {
+    const TileDims gd{c->g.nx, c->g.ny, xb, c->L.N};
+    if constexpr (std::is_same<S, QT>::value && !SR) {
+      if (c->stencil == LC_STENCIL_ISOTROPIC) {
+        hipLaunchKernelGGL((fused2d_step<S, DEV, TX, TY, MRT, QT, false, STENCIL_ISO>), dim3(bx, by),
+                           dim3(FUSED2D_NTHR), 0, st, q0, f0, f1, q1, gd, ctx_coef<S>(c), ctx_coef<QT>(c), 0u,
+                           StepRecord{});
+        return;
+      }
     }
-  }
-  hipLaunchKernelGGL((fused2d_step<S, DEV, TX, TY, MRT, QT, SR>), grid, dim3(FUSED2D_NTHR), 0, st, q0, f0, f1, q1, gd,
-                     ctx_coef<S>(c), ctx_coef<QT>(c), step_key(c->step), StepRecord{});
+    hipLaunchKernelGGL((fused2d_step<S, DEV, TX, TY, MRT, QT, SR>), dim3(bx, by), dim3(FUSED2D_NTHR), 0, st, q0, f0, f1,
+                       q1, gd, ctx_coef<S>(c), ctx_coef<QT>(c), step_key(c->step), StepRecord{});
+  });
 }
 
 // The same, recording for the reverse step (FP64, BGK, compact stencils).
@@ -422,11 +424,12 @@ template <int V>
 static void launch_fused2d_rec(lc_ctx* c, hipStream_t st, const double* f0, const double* q0, double* f1, double* q1,
                                const StepRecord& rec) {
   constexpr int TX = fused2d_tx(V), TY = fused2d_ty(V);
-  const GridDims gd{c->g.nx, c->g.ny, 1, c->L.N};
-  const dim3 grid((c->g.nx + TX - 1) / TX, (c->g.ny + TY - 1) / TY);
   const Coef<double> k = ctx_coef<double>(c);
-  hipLaunchKernelGGL((fused2d_step<double, false, TX, TY, false, double, false, STENCIL_COMPACT, true>), grid,
-                     dim3(FUSED2D_NTHR), 0, st, q0, f0, f1, q1, gd, k, k, 0u, rec);
+  tile_launches(c->g, TX, TY, FUSED2D_NTHR, [&](unsigned bx, unsigned by, int xb, int64_t) {
+    const TileDims gd{c->g.nx, c->g.ny, xb, c->L.N};
+    hipLaunchKernelGGL((fused2d_step<double, false, TX, TY, false, double, false, STENCIL_COMPACT, true>), dim3(bx, by),
+                       dim3(FUSED2D_NTHR), 0, st, q0, f0, f1, q1, gd, k, k, 0u, rec);
+  });
 }
 
 // One launch of the marching single pass.
@@ -494,7 +497,7 @@ static void step_fused_ptrs(lc_ctx* c, hipStream_t st, bool mark, const S* f0, c
 template <typename S, bool DEV, typename QT, bool MRT, bool SR>
 static void launch_fused2d_pair(lc_ctx* c, const S* f0, const QT* q0, S* f1, QT* q1) {
   constexpr int TX = FUSED2D_PAIR_TX, TY = FUSED2D_PAIR_TY;
-  const GridDims gd{c->g.nx, c->g.ny, 1, c->L.N};
+  const TileDims gd{c->g.nx, c->g.ny, 0, c->L.N};
   const dim3 grid((c->g.nx + TX - 1) / TX, (c->g.ny + TY - 1) / TY);
   const Coef<S> k = ctx_coef<S>(c);
   const Coef<QT> kq = ctx_coef<QT>(c);
@@ -918,10 +921,12 @@ struct VjpAdjoint {
 // The reverse of one step, given its forward quantities in v (rho, u, F,
 // predictor); parameter partials accumulate.
 static void vjp_reverse(lc_ctx* c, const VjpFields& v, const double* q_n, VjpAdjoint& a) {
-  const GridDims gd{c->g.nx, c->g.ny, 1, c->L.N};
-  const dim3 grid((c->g.nx + REV_TX - 1) / REV_TX, (c->g.ny + REV_TY - 1) / REV_TY);
-  hipLaunchKernelGGL(vjp_step, grid, dim3(REV_NTHR), 0, c->stream, a.f[a.cur], a.q[a.cur], a.f[a.cur ^ 1],
-                     a.q[a.cur ^ 1], q_n, v.qp, v.rho, v.u, v.F, v.part, gd, make_coef<double>(c->p));
+  tile_launches(c->g, REV_TX, REV_TY, REV_NTHR, [&](unsigned bx, unsigned by, int xb, int64_t before) {
+    const TileDims gd{c->g.nx, c->g.ny, xb, c->L.N};
+    hipLaunchKernelGGL(vjp_step, dim3(bx, by), dim3(REV_NTHR), 0, c->stream, a.f[a.cur], a.q[a.cur], a.f[a.cur ^ 1],
+                       a.q[a.cur ^ 1], q_n, v.qp, v.rho, v.u, v.F, v.part + 3 * before, gd,
+                       make_coef<double>(c->p));
+  });
   a.cur ^= 1;
 }
 

@@ -138,13 +138,13 @@ __device__ __forceinline__ void velgrad_lds(const double (*u)[RN], int k, double
 
 // One reverse step.  adj_f, adj_q: the adjoint of the state at step n+1;
 // out_f, out_q: that of step n.  Q, qp, rho, u, F: the forward quantities of
-// step n.  The parameter partials of the block's own sites are added to
-// part[block].
+// step n.  The launch takes the tiles of the columns from g.xb on; the parameter
+// partials of a block's own sites are added to part[block].
 __global__ void __launch_bounds__(REV_NTHR)
     vjp_step(const double* __restrict__ adj_f, const double* __restrict__ adj_q, double* __restrict__ out_f,
              double* __restrict__ out_q, const double* __restrict__ Q, const double* __restrict__ qp,
              const double* __restrict__ rho, const double* __restrict__ u, const double* __restrict__ F,
-             double* __restrict__ part, GridDims g, Coef<double> c) {
+             double* __restrict__ part, TileDims g, Coef<double> c) {
   using L = Lattice<0>;
   constexpr int TX = REV_TX, TY = REV_TY;
   using R4 = Rect<TX, TY, 4>;
@@ -170,7 +170,7 @@ __global__ void __launch_bounds__(REV_NTHR)
 
   const int tid = threadIdx.x, wave = tid / 64;
   const int blk = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
-  const int x0 = (blk % gridDim.x) * TX, y0 = (blk / gridDim.x) * TY;
+  const int x0 = g.xb + (blk % gridDim.x) * TX, y0 = (blk / gridDim.x) * TY;
   const size_t N = size_t(g.N);
   const bool near = g.nx >= R4::W && g.ny >= R4::H;  // the rectangle wraps at most once
   auto wrap = [&](int v, int n) { return near ? wrap_near(v, n) : wrapi(v, n); };

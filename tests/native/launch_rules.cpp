@@ -5,6 +5,16 @@ using namespace lc;
 
 extern "C" {
 int rule_num_cu() { return NUM_CU; }
+// out: blocks_x, blocks_y, xb, before of each launch
+int rule_tile_launches(const lc_grid* g, int tx, int ty, int threads, int64_t* out) {
+  int n = 0;
+  tile_launches(*g, tx, ty, threads, [&](unsigned bx, unsigned by, int xb, int64_t before) {
+    const int64_t v[4] = {bx, by, xb, before};
+    for (int k = 0; k < 4; k++) out[4 * n + k] = v[k];
+    n++;
+  });
+  return n;
+}
 int rule_auto_variant(const lc_grid* g) { return auto_variant(*g); }
 int rule_form2d(const lc_grid* g, int isotropic, int timed) { return fused2d_form(*g, isotropic != 0, timed != 0); }
 int rule_shape2d(const lc_grid* g) { return fused2d_shape(*g); }

@@ -76,3 +76,20 @@ def test_batch_of_the_strip_test_marches(rules):
     for shapes, takes in ((big, 1), (small, 0)):
         arr = (lc.lc_grid * len(shapes))(*[grid2d(nx, ny) for ny, nx in shapes])
         assert rules.rule_march_takes(len(shapes), arr) == takes
+
+
+@pytest.mark.parametrize("threads,tx,ty", [(1024, 32, 20), (1024, 16, 8), (768, 16, 16)])
+@pytest.mark.parametrize("nx,ny", [(1, 1), (301, 419), (1, 65535), (61000, 65535), ((1 << 27) - 32, 5), (1 << 27, 5),
+                                   ((1 << 27) + 1, 29), (1 << 28, 4), (89478485, 1), (89478500, 40), (1 << 30, 3)])
+def test_tiles_of_any_grid_fit_their_launches(rules, threads, tx, ty, nx, ny):
+    """Fewer than 2^32 threads along x in every launch; the launches take the
+    tile columns one after another, each once; rows that fit take one."""
+    out = (ctypes.c_int64 * 256)()
+    n = rules.rule_tile_launches(ref(grid2d(nx, ny)), tx, ty, threads, out)
+    ntx, nty = -(-nx // tx), -(-ny // ty)
+    column = 0
+    for k in range(n):
+        bx, by, xb, before = out[4 * k:4 * k + 4]
+        assert bx * threads < 1 << 32 and by == nty and xb == column * tx and before == column * nty
+        column += bx
+    assert column == ntx and (n == 1 or ntx * threads >= 1 << 32)
