@@ -65,13 +65,16 @@ inline int pick_chunk(int nz, int64_t tiles, int most, int extra, int resident =
 // Shapes of the single pass on two-dimensional grids (lc_fused2d.h): tiles of
 // TX x TY sites, all with 1024 threads.  A step of a small grid is a chain of
 // stages with a barrier between them, and a CU that holds one block spends the
-// chain once; so a grid takes the smallest tile with which it has at most one
-// tile per CU (16x8 up to 32x20, whose radius-3 rectangle of 38x26 points still
-// has one thread per point).  Measured per step in the mixed form on 301x419
+// chain once; so a grid takes the smallest tile of those with which the chip
+// goes through the fewest rounds of one tile per CU (16x8 up to 32x20, whose
+// radius-3 rectangle of 38x26 points still has one thread per point).  Measured per step in the mixed form on 301x419
 // sites: 15.4 us with 530 tiles of 32x8 sites and 512 threads (two rounds of
 // blocks), 9.7 us with 210 tiles of 32x20; on 256^2 sites (32x8 tiles)
 // 7.4 -> 7.1 us in FP64 and 5.9 -> 5.6 us in FP32, on 128x16 (16x8) 6.0 -> 4.9
-// us in FP64, against the same tiles without the overlap of their stages.
+// us in FP64, against the same tiles without the overlap of their stages.  With
+// more tiles than CUs, smallest with the fewest rounds against 32x20: 20000x7
+// (32x8) FP32 10.0 and 12.3 us, 400^2 (32x12) FP64 15.0 and 18.9, 448^2 (32x16)
+// FP64 18.8 and 20.6, FP32 9.4 and 10.6.
 constexpr int FUSED2D_NTHR = 1024;
 constexpr int FUSED2D_PAIR_TX = 16, FUSED2D_PAIR_TY = 8;  // tiles of two steps per launch
 constexpr int FUSED2D_NV = 5;
@@ -82,9 +85,11 @@ inline int64_t fused2d_tiles(const lc_grid& g, int v) {
   return int64_t((g.nx + fused2d_tx(v) - 1) / fused2d_tx(v)) * ((g.ny + fused2d_ty(v) - 1) / fused2d_ty(v));
 }
 inline int fused2d_shape(const lc_grid& g) {
-  for (int v = 0; v < FUSED2D_NV; v++)
-    if (fused2d_tiles(g, v) <= NUM_CU) return v;
-  return FUSED2D_NV - 1;
+  auto rounds = [&](int v) { return (fused2d_tiles(g, v) + NUM_CU - 1) / NUM_CU; };
+  int best = 0;
+  for (int v = 1; v < FUSED2D_NV; v++)
+    if (rounds(v) < rounds(best)) best = v;
+  return best;
 }
 inline bool fused2d_fits(const lc_grid& g) { return fused2d_tiles(g, FUSED2D_NV - 1) <= NUM_CU; }
 
@@ -154,7 +159,7 @@ inline Form2d fused2d_form(const lc_grid& g, bool isotropic, bool timed) {
   // two steps go in a launch where every 16x8 tile has a CU; not where
   // launches are timed one by one, nor in FP64 with the isotropic stencils,
   // whose larger first step spills (64^2 6.6 us per step in pairs against 6.2)
-  if (fused2d_shape(g) == 0 && !timed && !(g.precision == LC_FP64 && isotropic)) return FORM_PAIRS;
+  if (fused2d_tiles(g, 0) <= NUM_CU && !timed && !(g.precision == LC_FP64 && isotropic)) return FORM_PAIRS;
   return FORM_TILES;
 }
 

@@ -93,3 +93,16 @@ def test_tiles_of_any_grid_fit_their_launches(rules, threads, tx, ty, nx, ny):
         assert bx * threads < 1 << 32 and by == nty and xb == column * tx and before == column * nty
         column += bx
     assert column == ntx and (n == 1 or ntx * threads >= 1 << 32)
+
+
+# one tile per CU and more: the smallest tile with the fewest rounds
+SHAPE_OF = {(9000, 7): 1, (20000, 7): 1, (12000, 5): 1, (400, 400): 2, (70, 2000): 2, (448, 448): 3, (33, 4000): 3,
+            (540, 540): 4, (100, 100): 0, (256, 256): 1, (301, 419): 4}
+
+
+@pytest.mark.parametrize("nx,ny", SHAPE_OF)
+def test_tile_shape_has_the_fewest_rounds(rules, nx, ny):
+    g = grid2d(nx, ny)
+    rounds = [-(-rules.rule_tiles2d(ref(g), v) // rules.rule_num_cu()) for v in range(5)]
+    shape = rules.rule_shape2d(ref(g))
+    assert shape == rounds.index(min(rounds)) == SHAPE_OF[nx, ny]
