@@ -205,7 +205,9 @@ lc_status lc_set_params(lc_ctx *ctx, const lc_params *params);
  * default) picks the fastest the library provides for the context's stencil
  * and grid: the two-sweep variant on D3Q19, and on D2Q9 FUSED where the grid
  * fits the chip in one round of tiles (about 400^2 sites) or is large (from
- * 640^2 sites on), and the faster of the two in between.  FUSED runs every
+ * 640^2 sites on, if it fills three quarters of its strips of 56 columns; not
+ * where tens of thousands of columns leave the last round of strips nearly
+ * empty), and the faster of the two in between.  FUSED runs every
  * stage of a step in one pass over the grid: a block recomputes the
  * stress, moments and predictor on shrinking rings around its tile instead
  * of reading them back from HBM, or on large D2Q9 grids a wave marches
@@ -405,7 +407,8 @@ lc_status lc_step_static(const lc_grid *grid, const lc_params *params, void *con
  * q_offsets[k] bytes into each Q arena (5*N_k values, double in the mixed
  * form), in the single-grid layout.  A step of the batch is two kernel launches covering the tiles of
  * every grid, or one of the marching single pass (see lc_set_variant) where
- * the grids together have 640^2 sites or more (the same results bit for bit);
+ * the grids together have 640^2 sites or more, under the same conditions (the
+ * same results bit for bit);
  * runs of steps are captured once in a HIP graph (64 steps per
  * graph) and replayed on the batch stream.
  * ------------------------------------------------------------------------- */

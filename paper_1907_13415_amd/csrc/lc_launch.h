@@ -152,6 +152,34 @@ inline bool march_takes(int n, const lc_grid* g) {
   return sites >= MARCH_MIN_SITES && 4 * sites >= 3 * lanes;
 }
 
+// Whether the strips are expected to take at most as long as the two sweeps on
+// the grids they take.  The strips go through their chunks in rounds of
+// march_waves, and a round that is not full costs `part` of a full one at least;
+// a chunk repeats some rows (`more`), and tiles of the sweeps compute rows beyond
+// the grid (`idle`, their share of a row's time).  So where the strips alone
+// nearly fill the chip, and chunks can not be cut to fill it, the sweeps win.
+// Fitted to strips / sweeps measured on 4 to 96 rows, per part of the waves the
+// chip holds (FP64): 1.05 rounds 1.32 (8 rows), 1.19 (16), 1.09 (64); half a
+// round 1.13 (16), 1.20 (64); full rounds 0.89 (8), 0.77 (16), 0.72 (64).  FP32
+// with the compact stencils 0.43 to 1.03 everywhere.  Within 3% the strips stay.
+inline bool march_beats_sweeps(int n, const lc_grid* g, bool isotropic) {
+  const bool dq = double_q(g[0]);
+  if (!dq && g[0].precision != LC_FP32_SR && !isotropic) return true;
+  const double part = dq ? 0.59 : 0.51, more = dq ? 2.7 : 1.8, row = dq ? 0.67 : 0.64, idle = 0.5;
+  const int rows = march_rows(n, g);
+  double waves = 0.0, marched = 0.0, swept = 0.0;
+  for (int k = 0; k < n; k++) {
+    const double strips = double(march_strips(g[k])), chunks = (g[k].ny + rows - 1) / rows;
+    waves += strips * chunks;
+    marched += strips * g[k].ny;
+    swept += strips * (g[k].ny + idle * ((g[k].ny + 7) / 8 * 8 - g[k].ny));
+  }
+  const double most = march_waves(dq);
+  const double full = double(int64_t(waves / most)), rest = waves / most - full;
+  const double rounds = full + (rest > 0.0 ? part + (1.0 - part) * rest : 0.0);
+  return row * rounds * most * (marched / waves + more) <= 1.03 * swept;
+}
+
 // The form of a step of a two-dimensional grid in the single pass.
 enum Form2d { FORM_TILES, FORM_PAIRS, FORM_STRIPS };
 inline Form2d fused2d_form(const lc_grid& g, bool isotropic, bool timed) {
@@ -167,13 +195,14 @@ inline Form2d fused2d_form(const lc_grid& g, bool isotropic, bool timed) {
 // the single pass, in tiles where each has a CU of its own (launches are
 // latency bound there: 256^2 5.6 us per step in FP32 against 9.0 in two sweeps,
 // 7.1 against 10.0 in FP64; 384^2 8.0 against 11.1 and 11.5 against 14.7),
-// marching on large grids (march_takes); in between, up to 640^2 sites, in
-// tiles where Q is float (512^2 12.0 against 13.3 us, with the isotropic
+// marching on large grids (march_takes) unless the sweeps are faster there
+// (march_beats_sweeps); in between, up to 640^2 sites, in tiles where Q is float (512^2 12.0 against 13.3 us, with the isotropic
 // stencils 14.9 against 16.3), and the two sweeps elsewhere (448^2 in FP64
 // 18.7 against 20.5 us, mixed 16.2 against 17.6).
-inline int auto_variant(const lc_grid& g) {
+inline int auto_variant(const lc_grid& g, bool isotropic) {
   if (g.lattice != LC_D2Q9) return LC_VARIANT_SPLIT;
-  if (fused2d_fits(g) || march_takes(1, &g) || (!double_q(g) && int64_t(g.nx) * g.ny < MARCH_MIN_SITES))
+  if (fused2d_fits(g) || (march_takes(1, &g) && march_beats_sweeps(1, &g, isotropic)) ||
+      (!double_q(g) && int64_t(g.nx) * g.ny < MARCH_MIN_SITES))
     return LC_VARIANT_FUSED;
   return LC_VARIANT_SPLIT;
 }

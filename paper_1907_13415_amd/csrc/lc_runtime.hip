@@ -570,7 +570,7 @@ static lc_status run_steps_split(lc_ctx* c, int64_t n) {
 
 template <int LAT, typename S, bool DEV, typename QT = S>
 static lc_status run_steps(lc_ctx* c, int64_t n) {
-  const int v = c->variant == LC_VARIANT_AUTO ? auto_variant(c->g) : c->variant;
+  const int v = c->variant == LC_VARIANT_AUTO ? auto_variant(c->g, c->stencil == LC_STENCIL_ISOTROPIC) : c->variant;
   if (c->stencil == LC_STENCIL_ISOTROPIC && v == LC_VARIANT_FUSED && c->g.lattice != LC_D2Q9)
     return fail(LC_EUNSUPPORTED, "the single pass takes the isotropic stencils on D2Q9 grids only");
   if (v == LC_VARIANT_SPLIT) return run_steps_split<LAT, S, DEV, QT>(c, n);
@@ -1654,7 +1654,7 @@ lc_status lc_batch_init(int32_t ngrids, const lc_grid* grids, const lc_params* p
   b->stream = static_cast<hipStream_t>(stream);
   b->B = B;
   b->vt[0] = b->vt[1] = 0;
-  b->march = march_takes(ngrids, grids);
+  b->march = march_takes(ngrids, grids) && march_beats_sweeps(ngrids, grids, false);
   b->parity = 0;
   b->step = 0;
   b->loaded = false;

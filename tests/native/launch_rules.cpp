@@ -15,10 +15,13 @@ int rule_tile_launches(const lc_grid* g, int tx, int ty, int threads, int64_t* o
   });
   return n;
 }
-int rule_auto_variant(const lc_grid* g) { return auto_variant(*g); }
+int rule_auto_variant(const lc_grid* g, int isotropic) { return auto_variant(*g, isotropic != 0); }
 int rule_form2d(const lc_grid* g, int isotropic, int timed) { return fused2d_form(*g, isotropic != 0, timed != 0); }
 int rule_shape2d(const lc_grid* g) { return fused2d_shape(*g); }
 int64_t rule_tiles2d(const lc_grid* g, int v) { return fused2d_tiles(*g, v); }
 int rule_march_takes(int n, const lc_grid* g) { return march_takes(n, g); }
+int rule_march_beats_sweeps(int n, const lc_grid* g, int isotropic) {
+  return march_beats_sweeps(n, g, isotropic != 0);
+}
 int rule_march_rows(int n, const lc_grid* g) { return march_rows(n, g); }
 }

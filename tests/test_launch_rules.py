@@ -65,7 +65,7 @@ def test_steps_that_are_not_paired(rules):
     ("fp32sr", 639, 640, lc.LC_VARIANT_FUSED), ("fp64", 640, 640, lc.LC_VARIANT_FUSED),
     ("fp64", 639, 640, lc.LC_VARIANT_SPLIT), ("fp32dev", 64, 7000, lc.LC_VARIANT_SPLIT)])
 def test_auto_variant_at_its_thresholds(rules, precision, nx, ny, variant):
-    assert rules.rule_auto_variant(ref(grid2d(nx, ny, precision))) == variant
+    assert rules.rule_auto_variant(ref(grid2d(nx, ny, precision)), 0) == variant
 
 
 def test_batch_of_the_strip_test_marches(rules):
@@ -106,3 +106,33 @@ def test_tile_shape_has_the_fewest_rounds(rules, nx, ny):
     rounds = [-(-rules.rule_tiles2d(ref(g), v) // rules.rule_num_cu()) for v in range(5)]
     shape = rules.rule_shape2d(ref(g))
     assert shape == rounds.index(min(rounds)) == SHAPE_OF[nx, ny]
+
+
+SWEEPS, SINGLE = lc.LC_VARIANT_SPLIT, lc.LC_VARIANT_FUSED
+
+
+@pytest.mark.parametrize("precision,iso,nx,ny,variant", [
+    # strips that nearly fill, or just overfill, the waves the chip holds
+    ("fp64", 0, 65000, 7, SWEEPS), ("mixed", 0, 65000, 7, SWEEPS), ("fp64", 0, 60000, 8, SWEEPS),
+    ("fp64", 1, 65000, 7, SWEEPS), ("fp64", 0, 1075 * 56, 64, SWEEPS), ("mixed", 0, 522 * 56, 64, SWEEPS),
+    ("fp32dev", 1, 1044 * 56, 16, SWEEPS), ("fp32sr", 0, 1126 * 56, 8, SWEEPS),
+    # full rounds, many rounds, FP32, tiles with idle rows
+    ("fp64", 0, 1003 * 56, 8, SINGLE), ("fp64", 0, 2027 * 56, 16, SINGLE), ("fp64", 0, 65000, 9, SINGLE),
+    ("fp64", 0, 410000, 1, SINGLE), ("mixed", 0, 410000, 1, SINGLE), ("fp32dev", 0, 65000, 7, SINGLE),
+    ("fp32dev", 0, 1044 * 56, 16, SINGLE), ("fp64", 0, 501 * 56, 64, SINGLE), ("fp64", 0, 640, 640, SINGLE),
+    ("mixed", 0, 1000, 1000, SINGLE), ("fp64", 1, 700, 700, SINGLE), ("fp64", 0, 56, 8000, SINGLE),
+    ("fp64", 0, 2048, 2048, SINGLE), ("fp32sr", 0, 640, 640, SINGLE)])
+def test_strips_only_where_they_beat_the_sweeps(rules, precision, iso, nx, ny, variant):
+    """As measured: on grids of very many columns a march over the whole
+    height leaves the chip part empty in its last round."""
+    g = grid2d(nx, ny, precision)
+    assert rules.rule_march_takes(1, ref(g)) == 1
+    assert rules.rule_auto_variant(ref(g), iso) == variant
+
+
+def test_batch_of_wide_short_grids_takes_the_sweeps(rules):
+    """60 grids of 2048x7: 2220 strips for 1024 waves."""
+    arr = (lc.lc_grid * 60)(*[grid2d(2048, 7, "mixed")] * 60)
+    assert rules.rule_march_takes(60, arr) == 1 and rules.rule_march_beats_sweeps(60, arr, 0) == 0
+    arr = (lc.lc_grid * 64)(*[grid2d(300, 300, "mixed")] * 64)
+    assert rules.rule_march_beats_sweeps(64, arr, 0) == 1
