@@ -207,4 +207,19 @@ inline int auto_variant(const lc_grid& g, bool isotropic) {
   return LC_VARIANT_SPLIT;
 }
 
+// Tiles of the reverse step (lc_vjp.h), one block of REV_NTHR threads each:
+// 16x16 sites, or 40x4 on grids of few rows, the one with fewer rounds of one
+// tile per CU.  A step of a segment on 30000x3 sites: 116.9 us in 16x16, 56.7 in
+// 40x4 (60.2 in the 64x4 blocks of three kernels).
+constexpr int REV_NTHR = 768, REV_NV = 2;
+constexpr int rev_tx(int v) { return v == 0 ? 16 : 40; }
+constexpr int rev_ty(int v) { return v == 0 ? 16 : 4; }
+inline int64_t rev_tiles(const lc_grid& g, int v) {
+  return (int64_t(g.nx) + rev_tx(v) - 1) / rev_tx(v) * ((g.ny + rev_ty(v) - 1) / rev_ty(v));
+}
+inline int rev_shape(const lc_grid& g) {
+  auto rounds = [&](int v) { return (rev_tiles(g, v) + NUM_CU - 1) / NUM_CU; };
+  return rounds(1) < rounds(0) ? 1 : 0;
+}
+
 }  // namespace lc

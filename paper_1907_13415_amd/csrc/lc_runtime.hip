@@ -129,7 +129,7 @@ Layout layout_of(const lc_grid& g) {
   L.off_vjp = off;
   if (g.lattice == LC_D2Q9 && g.precision == LC_FP64) {
     off = up(off + size_t(VJP_COMPS) * N * 8);
-    off = up(off + size_t(vjp_tiles(g.nx, g.ny)) * 3 * 8);
+    off = up(off + size_t(rev_tiles(g, rev_shape(g))) * 3 * 8);
   }
   L.scratch_bytes = off;
   return L;
@@ -904,7 +904,7 @@ static VjpFields vjp_fields(lc_ctx* c) {
   v.r = take(5);
   v.adj_f = take(9);
   v.adj_q = take(5);
-  v.nblocks = vjp_tiles(c->g.nx, c->g.ny);
+  v.nblocks = rev_tiles(c->g, rev_shape(c->g));
   // the partials follow at the next 256-byte boundary, as laid out
   v.part = reinterpret_cast<double*>((reinterpret_cast<uintptr_t>(base + size_t(VJP_COMPS) * N) + 255) &
                                      ~uintptr_t(255));
@@ -918,15 +918,25 @@ struct VjpAdjoint {
   int cur = 0;
 };
 
+template <int V>
+static void launch_vjp_step(lc_ctx* c, const VjpFields& v, const double* q_n, const VjpAdjoint& a) {
+  constexpr int TX = rev_tx(V), TY = rev_ty(V);
+  tile_launches(c->g, TX, TY, REV_NTHR, [&](unsigned bx, unsigned by, int xb, int64_t before) {
+    const TileDims gd{c->g.nx, c->g.ny, xb, c->L.N};
+    hipLaunchKernelGGL((vjp_step<TX, TY>), dim3(bx, by), dim3(REV_NTHR), 0, c->stream, a.f[a.cur], a.q[a.cur],
+                       a.f[a.cur ^ 1], a.q[a.cur ^ 1], q_n, v.qp, v.rho, v.u, v.F, v.part + 3 * before, gd,
+                       make_coef<double>(c->p));
+  });
+}
+
 // The reverse of one step, given its forward quantities in v (rho, u, F,
 // predictor); parameter partials accumulate.
 static void vjp_reverse(lc_ctx* c, const VjpFields& v, const double* q_n, VjpAdjoint& a) {
-  tile_launches(c->g, REV_TX, REV_TY, REV_NTHR, [&](unsigned bx, unsigned by, int xb, int64_t before) {
-    const TileDims gd{c->g.nx, c->g.ny, xb, c->L.N};
-    hipLaunchKernelGGL(vjp_step, dim3(bx, by), dim3(REV_NTHR), 0, c->stream, a.f[a.cur], a.q[a.cur], a.f[a.cur ^ 1],
-                       a.q[a.cur ^ 1], q_n, v.qp, v.rho, v.u, v.F, v.part + 3 * before, gd,
-                       make_coef<double>(c->p));
-  });
+  static_assert(REV_NV == 2, "one launch branch per tile shape");
+  if (rev_shape(c->g) == 0)
+    launch_vjp_step<0>(c, v, q_n, a);
+  else
+    launch_vjp_step<1>(c, v, q_n, a);
   a.cur ^= 1;
 }
 

@@ -11,8 +11,8 @@
 // self-adjoint and the central difference D has adjoint -D on a periodic
 // grid.
 //
-// One launch per reverse step, one block of 768 threads per 16x16 tile.  As
-// in the single pass of the forward step, the stages run on rectangles that
+// One launch per reverse step, one block of 768 threads per tile of 16x16
+// sites (40x4 on grids of few rows, rev_shape).  As in the single pass of the forward step, the stages run on rectangles that
 // shrink by one site per gather (both rates on radius 3, collision and
 // force-corrected velocity on 2, stress and molecular field on 1, the
 // order-tensor adjoint on the tile) and hand their fields on in LDS, so a site
@@ -42,12 +42,6 @@ struct VjpFields {
   int64_t nblocks;
 };
 constexpr int VJP_COMPS = 4 + 1 + 2 + 2 + 5 + 5 + 9 + 5;
-
-// tiles of the reverse step
-constexpr int REV_TX = 16, REV_TY = 16, REV_NTHR = 768;
-inline int64_t vjp_tiles(int nx, int ny) {
-  return int64_t((nx + REV_TX - 1) / REV_TX) * ((ny + REV_TY - 1) / REV_TY);
-}
 
 __device__ __forceinline__ void block_reduce3(double (&v)[3], double* __restrict__ dst) {
   __shared__ double part[16][3];
@@ -140,13 +134,13 @@ __device__ __forceinline__ void velgrad_lds(const double (*u)[RN], int k, double
 // out_f, out_q: that of step n.  Q, qp, rho, u, F: the forward quantities of
 // step n.  The launch takes the tiles of the columns from g.xb on; the parameter
 // partials of a block's own sites are added to part[block].
+template <int TX, int TY>
 __global__ void __launch_bounds__(REV_NTHR)
     vjp_step(const double* __restrict__ adj_f, const double* __restrict__ adj_q, double* __restrict__ out_f,
              double* __restrict__ out_q, const double* __restrict__ Q, const double* __restrict__ qp,
              const double* __restrict__ rho, const double* __restrict__ u, const double* __restrict__ F,
              double* __restrict__ part, TileDims g, Coef<double> c) {
   using L = Lattice<0>;
-  constexpr int TX = REV_TX, TY = REV_TY;
   using R4 = Rect<TX, TY, 4>;
   using R3 = Rect<TX, TY, 3>;
   using R2 = Rect<TX, TY, 2>;

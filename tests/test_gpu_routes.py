@@ -5,6 +5,7 @@ import pytest
 
 from paper_1907_13415_amd import inputs
 from gpu_util import require_gpu
+from test_gpu_vjp_tiles import test_reverse_step_at_tile_edges as reverse_step
 
 pytestmark = pytest.mark.gpu
 
@@ -34,3 +35,11 @@ def _equal_to_two_sweeps(nx, ny, precision, iso):
 def test_more_tiles_than_compute_units(nx, ny, precision, iso):
     """Two rounds of tiles of 32x8, 32x12 and 32x16 sites."""
     _equal_to_two_sweeps(nx, ny, precision, iso)
+
+
+# against autograd of the CPU twin, to the bounds of the other tile shape's test
+@pytest.mark.parametrize("nx,ny,steps", [(4097, 3, 1), (4120, 4, 2), (5119, 8, 1), (10300, 1, 1)])
+def test_reverse_step_in_flat_tiles(nx, ny, steps):
+    """40x4 tiles: one short row of tiles, whole tiles, two rows of tiles, a
+    single row of sites; last tiles narrower and of whole width."""
+    reverse_step(nx, ny, steps)

@@ -78,7 +78,7 @@ def test_batch_of_the_strip_test_marches(rules):
         assert rules.rule_march_takes(len(shapes), arr) == takes
 
 
-@pytest.mark.parametrize("threads,tx,ty", [(1024, 32, 20), (1024, 16, 8), (768, 16, 16)])
+@pytest.mark.parametrize("threads,tx,ty", [(1024, 32, 20), (1024, 16, 8), (768, 16, 16), (768, 40, 4)])
 @pytest.mark.parametrize("nx,ny", [(1, 1), (301, 419), (1, 65535), (61000, 65535), ((1 << 27) - 32, 5), (1 << 27, 5),
                                    ((1 << 27) + 1, 29), (1 << 28, 4), (89478485, 1), (89478500, 40), (1 << 30, 3)])
 def test_tiles_of_any_grid_fit_their_launches(rules, threads, tx, ty, nx, ny):
@@ -136,3 +136,10 @@ def test_batch_of_wide_short_grids_takes_the_sweeps(rules):
     assert rules.rule_march_takes(60, arr) == 1 and rules.rule_march_beats_sweeps(60, arr, 0) == 0
     arr = (lc.lc_grid * 64)(*[grid2d(300, 300, "mixed")] * 64)
     assert rules.rule_march_beats_sweeps(64, arr, 0) == 1
+
+
+@pytest.mark.parametrize("nx,ny,shape", [(4096, 3, 0), (4097, 3, 1), (30000, 3, 1), (5120, 8, 1), (5200, 8, 0), (30000, 9, 0),
+                                         (256, 256, 0), (1, 4000, 0), (2048, 2048, 0)])
+def test_reverse_tiles_of_few_rows(rules, nx, ny, shape):
+    """40x4 tiles where they go through the chip in fewer rounds than 16x16."""
+    assert rules.rule_rev_shape(ref(grid2d(nx, ny, "fp64"))) == shape
