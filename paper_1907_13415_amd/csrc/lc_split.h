@@ -268,6 +268,35 @@ __device__ __forceinline__ void store_region(const RegionRegs<S, TX, TY, NC>& r,
   }
 }
 
+// The same without registers between: the points one after another, each loaded
+// and stored before the next.  For the tiles of 1024 threads, and of 512 where Q
+// is double: a CU holds one or two of those blocks, so every load in flight at
+// once delays the halo that the whole block waits for, and the waves have no
+// registers to spare.  A step of 64 grids (64^2 to 512^2, FP64) with 64x16 tiles
+// 363 us with all loads in flight and 324 one by one, with 64x8 331 and 327; in
+// FP32 with 64x8 tiles of 64 grids of 64^2 11.9 and 12.5, so those stay.
+template <typename S, int TX, int TY, int NC, typename SRC>
+__device__ __forceinline__ void load_region(S* dst, const SRC& src, const RegionIdx<TX, TY>& idx, int gz,
+                                            const GridDims& g, int tid) {
+  using I = RegionIdx<TX, TY>;
+  const uint32_t plane = uint32_t(g.nx) * uint32_t(g.ny) * uint32_t(gz);
+#pragma unroll 1
+  for (int p = 0; p < I::P; p++) {
+    const int k = tid + p * I::NT;
+    if (k >= I::R2) break;
+    uint32_t off = idx.off[0];
+#pragma unroll
+    for (int w = 1; w < I::P; w++) off = p == w ? idx.off[w] : off;
+    const uint32_t s = plane + off;
+#pragma unroll
+    for (int q = 0; q < NC; q++) dst[q * I::R2 + k] = src(q, s);
+  }
+}
+template <typename S, int TX, int TY>
+constexpr bool one_by_one() {
+  return TX * TY >= 1024 || (TX * TY >= 512 && sizeof(S) == 8);
+}
+
 // Q(n+1) = Q + (R(Q) + R(Q^P))/2 (Sec. 1.2.2, step 5) at site s;
 // with SR the float sums are rounded stochastically, one uniform number per
 // site (from the site index and the step's key) serving its five
@@ -565,13 +594,19 @@ __device__ __forceinline__ void split_lb_body(const QT* __restrict__ Qin, const 
 
   const RegionIdx<TX, TY> ridx(x0, y0, g, tid);
   if constexpr (DIM == 2) {
-    RegionRegs<QT, TX, TY, 5> rq;
-    fetch_region<QT, TX, TY, 5>(rq, qsrc, ridx, 0, g, tid);
     QT tz[3];
     S f[L::q];
-    fetch_f(0, f);
-    store_region<QT, TX, TY, 5>(rq, &sQ[0][0][0], tid);
-    __syncthreads();
+    if constexpr (one_by_one<QT, TX, TY>()) {
+      load_region<QT, TX, TY, 5>(&sQ[0][0][0], qsrc, ridx, 0, g, tid);
+      __syncthreads();
+      fetch_f(0, f);
+    } else {
+      RegionRegs<QT, TX, TY, 5> rq;
+      fetch_region<QT, TX, TY, 5>(rq, qsrc, ridx, 0, g, tid);
+      fetch_f(0, f);
+      store_region<QT, TX, TY, 5>(rq, &sQ[0][0][0], tid);
+      __syncthreads();
+    }
     tau_plane(0, 0, 0, 0, tz);
     __syncthreads();
     lb_site(0, 0, tz, tz, f);
@@ -804,9 +839,13 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
 
   const RegionIdx<TX, TY> ridx(x0, y0, g, tid);
   if constexpr (DIM == 2) {
-    RegionRegs<S, TX, TY, NC> rq;
-    fetch_region<S, TX, TY, NC>(rq, csrc, ridx, 0, g, tid);
-    store_region<S, TX, TY, NC>(rq, &sQ[0][0][0], tid);
+    if constexpr (one_by_one<S, TX, TY>()) {
+      load_region<S, TX, TY, NC>(&sQ[0][0][0], csrc, ridx, 0, g, tid);
+    } else {
+      RegionRegs<S, TX, TY, NC> rq;
+      fetch_region<S, TX, TY, NC>(rq, csrc, ridx, 0, g, tid);
+      store_region<S, TX, TY, NC>(rq, &sQ[0][0][0], tid);
+    }
     __syncthreads();
     Stash st;
     const Sym<S> pc = pred_point(0, 0, 0, tx + 1, ty + 1, st);
