@@ -33,6 +33,11 @@ inline void tile_launches(const lc_grid& g, int tx, int ty, int threads, LAUNCH 
     launch(unsigned(std::min(most, ntx - t)), unsigned(nty), int(t * tx), t * nty);
 }
 
+// Whether the coordinates x0 - 2 .. x0 + t + 1 of a tile of t >= 2 sites from x0
+// on (a multiple of t within the grid) are in -n .. 2n - 1, so that they wrap at
+// most once.
+constexpr bool region_wraps_once(int n, int t) { return n >= 2 && 2 * int64_t(n) >= t + 2; }
+
 // Planes per block along z for a sweep of `tiles` column tiles on a grid of
 // nz planes, at most `most`.  A block of zc planes marches zc + `extra`
 // planes, one after another, so a grid with few tiles is bound by that serial

@@ -203,16 +203,18 @@ __device__ __forceinline__ int wrap_near(int v, int n) { return v < 0 ? v + n : 
 
 // The R2 region of a block, one point per thread and pass: the in-plane
 // (periodic) site index of each of the thread's points, formed once per
-// block.  Tiles at least as wide as the grid may wrap more than once and
-// take the division; all others do without (a runtime division costs some
-// 20 instructions, and there are two per point).
+// block.  A region wraps at most once unless the grid is about half as wide as
+// the tile or less (region_wraps_once); those take the division, all others do
+// without (a runtime division costs some 20 instructions, and there are two per
+// point, before the first load: 64 grids of 64^2 in 64x16 tiles, FP32, 11.1 us per
+// step with it and 10.7 without).
 template <int TX, int TY>
 struct RegionIdx {
   static constexpr int W2 = TX + 4, R2 = (TX + 4) * (TY + 4), NT = TX * TY;
   static constexpr int P = (R2 + NT - 1) / NT;  // points per thread
   uint32_t off[P];
   __device__ __forceinline__ RegionIdx(int x0, int y0, const GridDims& g, int tid) {
-    if (g.nx >= TX + 4 && g.ny >= TY + 4) {
+    if (region_wraps_once(g.nx, TX) && region_wraps_once(g.ny, TY)) {
 #pragma unroll
       for (int p = 0; p < P; p++) {
         const int k = tid + p * NT;

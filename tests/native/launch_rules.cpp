@@ -19,6 +19,7 @@ int rule_auto_variant(const lc_grid* g, int isotropic) { return auto_variant(*g,
 int rule_form2d(const lc_grid* g, int isotropic, int timed) { return fused2d_form(*g, isotropic != 0, timed != 0); }
 int rule_shape2d(const lc_grid* g) { return fused2d_shape(*g); }
 int64_t rule_tiles2d(const lc_grid* g, int v) { return fused2d_tiles(*g, v); }
+int rule_region_wraps_once(int n, int t) { return region_wraps_once(n, t); }
 int rule_rev_shape(const lc_grid* g) { return rev_shape(*g); }
 int rule_march_takes(int n, const lc_grid* g) { return march_takes(n, g); }
 int rule_march_beats_sweeps(int n, const lc_grid* g, int isotropic) {

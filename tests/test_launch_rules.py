@@ -143,3 +143,16 @@ def test_batch_of_wide_short_grids_takes_the_sweeps(rules):
 def test_reverse_tiles_of_few_rows(rules, nx, ny, shape):
     """40x4 tiles where they go through the chip in fewer rounds than 16x16."""
     assert rules.rule_rev_shape(ref(grid2d(nx, ny, "fp64"))) == shape
+
+
+def test_regions_that_wrap_once(rules):
+    """The rule that spares a tile's halo region the division, against the
+    coordinates themselves: never where one is beyond the next period, and on
+    every grid at least as wide as the tile."""
+    for t in (4, 8, 16, 32, 64, 128):
+        for n in list(range(1, 3 * t + 3)) + [1 << 20, 1 << 30]:
+            x0s = range(0, n, t) if n < 1 << 20 else (0, (n - 1) // t * t)
+            once = all(-n <= x0 - 2 and x0 + t + 1 < 2 * n for x0 in x0s)
+            rule = rules.rule_region_wraps_once(n, t) == 1
+            assert rule == once, (n, t)
+            assert once or n < t
