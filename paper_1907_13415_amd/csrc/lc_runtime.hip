@@ -314,14 +314,14 @@ static bool stream_stores(const lc_grid& g, size_t size) {
   return size_t(g.nx) * size % 64 == 0 && 2 * sites * (Lattice<LAT>::q * sizeof(S) + 5 * sizeof(QT)) > (size_t(256) << 20);
 }
 
-// The chunks of the context's steps: as set by lc_set_chunk, else by
+// The chunks of the context's steps: as set by lc_set_chunk, cut evenly, else by
 // pick_chunk (once per call, not per step).  Chunks longer than the grid are
 // the whole depth (the block index arithmetic stays within int).
 template <int LAT, typename S, typename QT>
 static Chunks split_chunks(const lc_ctx* c) {
   using C = SplitCfg<LAT, QT, S>;
   if constexpr (!C::d3) return Chunks{1, 1};
-  if (c->zchunk > 0) return Chunks{std::min(c->zchunk, c->g.nz), std::min(c->zchunk, c->g.nz)};
+  if (c->zchunk > 0) return Chunks{even_chunk(c->g.nz, c->zchunk), even_chunk(c->g.nz, c->zchunk)};
   auto tiles = [&](int tx, int ty) { return int64_t((c->g.nx + tx - 1) / tx) * ((c->g.ny + ty - 1) / ty); };
   const bool iso = c->stencil == LC_STENCIL_ISOTROPIC;
   // MRT and the isotropic stencils march up to 32 planes in the float
@@ -456,7 +456,9 @@ static void step_fused_form(lc_ctx* c, hipStream_t st, const S* f0, const QT* q0
   if constexpr (Lattice<LAT>::dim == 3) {
     using C = FusedCfg<QT>;
     const int64_t tiles = int64_t((c->g.nx + C::TX - 1) / C::TX) * ((c->g.ny + C::TY - 1) / C::TY);
-    const int zc = c->zchunk > 0 ? std::min(c->zchunk, c->g.nz) : pick_chunk(c->g.nz, tiles, C::ZC, 8, 1);
+    // 2000x40x40 (z first) in FP64: 1113 us in 510 blocks of 59 planes, 1062 in
+    // 480 of 63, where the estimate is 7% in favour of the former
+    const int zc = c->zchunk > 0 ? even_chunk(c->g.nz, c->zchunk) : pick_chunk(c->g.nz, tiles, C::ZC, 8, 1, 0.08);
     launch_fused3d<S, DEV, QT, MRT, SR>(c, st, zc, f0, q0, f1, q1);
   } else {
     if (fused2d_form(c->g, c->stencil == LC_STENCIL_ISOTROPIC, c->timing) == FORM_STRIPS) {

@@ -20,6 +20,10 @@ int rule_form2d(const lc_grid* g, int isotropic, int timed) { return fused2d_for
 int rule_shape2d(const lc_grid* g) { return fused2d_shape(*g); }
 int64_t rule_tiles2d(const lc_grid* g, int v) { return fused2d_tiles(*g, v); }
 int rule_region_wraps_once(int n, int t) { return region_wraps_once(n, t); }
+int rule_pick_chunk(int nz, int tiles, int most, int extra, int resident, double margin) {
+  return pick_chunk(nz, tiles, most, extra, resident, margin);
+}
+int rule_even_chunk(int nz, int planes) { return even_chunk(nz, planes); }
 int rule_rev_shape(const lc_grid* g) { return rev_shape(*g); }
 int rule_march_takes(int n, const lc_grid* g) { return march_takes(n, g); }
 int rule_march_beats_sweeps(int n, const lc_grid* g, int isotropic) {

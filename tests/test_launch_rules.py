@@ -156,3 +156,20 @@ def test_regions_that_wrap_once(rules):
             rule = rules.rule_region_wraps_once(n, t) == 1
             assert rule == once, (n, t)
             assert once or n < t
+
+
+@pytest.mark.parametrize("nz,tiles,margin,chunk", [(2000, 15, 0.08, 63), (2000, 15, 0.0, 59), (33, 380, 0.08, 17),
+                                                   (500, 32, 0.08, 63), (96, 36, 0.08, 14), (256, 256, 0.08, 64),
+                                                   (1, 1, 0.08, 1), (64, 1, 0.08, 1)])
+def test_chunks_of_the_3d_single_pass(rules, nz, tiles, margin, chunk):
+    """Shorter chunks in more blocks only where the estimate is clearly in
+    their favour, even ones of the longest otherwise."""
+    assert rules.rule_pick_chunk(nz, tiles, 64, 8, 1, ctypes.c_double(margin)) == chunk
+
+
+@pytest.mark.parametrize("nz,planes,chunk", [(200, 33, 29), (200, 128, 100), (200, 100, 100), (200, 1, 1), (200, 200, 200),
+                                             (33, 8, 7), (7, 2**31 - 1, 7), (65535, 65534, 32768), (1, 5, 1)])
+def test_chunks_asked_for_are_cut_evenly(rules, nz, planes, chunk):
+    """As many chunks as asked for, none longer, none much shorter."""
+    assert rules.rule_even_chunk(nz, planes) == chunk
+    assert -(-nz // chunk) == -(-nz // min(planes, nz)) and chunk <= planes
