@@ -349,10 +349,10 @@ def run_batch(torch, lc, stream, dev, steps, tiles=None, physics=True):
         for k, w in enumerate(ws):
             b.load(k, w.q5)
         if tiles is None:
-            tile, _ = b.autotune(10)
+            b.autotune(10)
         else:
             b.set_tiles(*tiles)
-            tile = tiles[0] + 7 * tiles[1]
+        strips, v_lb, v_q = b.launch()
         for k, w in enumerate(ws):
             b.load(k, w.q5)
         b.step(64)
@@ -385,7 +385,8 @@ def run_batch(torch, lc, stream, dev, steps, tiles=None, physics=True):
         del bs
     sites = sum(w.shape[1] * w.shape[2] for w in ws)
     shapes_ = ["32x8", "64x4", "16x16", "32x16", "64x8", "64x16", "128x8"]
-    return dict(grids=len(ws), sites=sites, tiles={"lb": shapes_[tile % 7], "q": shapes_[tile // 7]},
+    return dict(grids=len(ws), sites=sites, form="strips" if strips else "two sweeps",
+                tiles=None if strips else {"lb": shapes_[v_lb], "q": shapes_[v_q]},
                 ms_per_step=round(ms, 5),
                 mlups=round(sites / (ms * 1e-3) / 1e6, 2),
                 roofline_frac=round(alg_bytes_per_site(9, 4) * sites / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),

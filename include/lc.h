@@ -445,6 +445,23 @@ lc_status lc_batch_step(lc_batch *b, int64_t n);
  * 0..6. */
 lc_status lc_batch_set_tiles(lc_batch *b, int32_t v_lb, int32_t v_q);
 
+/* The launches of a step of the batch: *strips = 1 where it is one launch of
+ * the marching single pass, 0 where it is the two sweeps; *v_lb, *v_q the tile
+ * shapes of the sweeps, also while the strips run.  Two batches of the same
+ * grids run alike after
+ *   lc_batch_get_launch(a, &s, &l, &q);
+ *   lc_batch_set_tiles(b, l, q);
+ *   lc_batch_set_strips(b, s);
+ * Any output pointer may be NULL.  Library plumbing.  LC_EINVAL for a NULL
+ * batch. */
+lc_status lc_batch_get_launch(const lc_batch *b, int32_t *strips, int32_t *v_lb, int32_t *v_q);
+
+/* Run the marching single pass (strips != 0) or the two sweeps with their
+ * present tile shapes (0).  A launch shape: implements no passage of the paper
+ * and does not change results.  LC_EUNSUPPORTED for strips on a batch with a
+ * grid of more than 2^29 sites. */
+lc_status lc_batch_set_strips(lc_batch *b, int32_t strips);
+
 /* lc_batch_set_tiles(b, variant, variant).  A launch shape: implements no
  * passage of the paper and does not change results. */
 lc_status lc_batch_set_tile(lc_batch *b, int32_t variant);
@@ -467,7 +484,8 @@ lc_status lc_batch_set_collision(lc_batch *b, int32_t kind, const double *rates,
 /* Time every pair of tile shapes for trial_steps steps (after one untimed
  * step) with HIP events and keep the fastest; *chosen = v_lb + 7 * v_q.  The
  * marching single pass is timed as well and kept if it is faster than every
- * pair (*ms_per_step is its time then).
+ * pair: *ms_per_step is its time then, *chosen still the fastest pair, and
+ * lc_batch_get_launch tells which of the two the batch runs.
  * The state advances by 49 * (trial_steps + 1) steps: tune before loading
  * the real state, or load it again afterwards.  Synchronises the stream.
  * Measurement plumbing: implements no passage of the paper. */

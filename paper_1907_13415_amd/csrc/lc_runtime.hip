@@ -1809,6 +1809,25 @@ lc_status lc_batch_set_tiles(lc_batch* b, int32_t v_lb, int32_t v_q) {
   return hip_check(hipStreamSynchronize(b->stream), "descriptor upload sync");
 }
 
+lc_status lc_batch_get_launch(const lc_batch* b, int32_t* strips, int32_t* v_lb, int32_t* v_q) {
+  clear_error();
+  if (!b) return fail(LC_EINVAL, "batch is NULL");
+  if (strips) *strips = b->march ? 1 : 0;
+  if (v_lb) *v_lb = b->vt[0];
+  if (v_q) *v_q = b->vt[1];
+  return LC_OK;
+}
+
+lc_status lc_batch_set_strips(lc_batch* b, int32_t strips) {
+  clear_error();
+  if (!b) return fail(LC_EINVAL, "batch is NULL");
+  if (strips && !b->B.march_tiles) return fail(LC_EUNSUPPORTED, "a grid of the batch is too large for the strips");
+  if (b->march == (strips != 0)) return LC_OK;
+  b->march = strips != 0;
+  batch_drop_graphs(b);
+  return LC_OK;
+}
+
 lc_status lc_batch_set_tile(lc_batch* b, int32_t variant) { return lc_batch_set_tiles(b, variant, variant); }
 
 lc_status lc_batch_set_stencil(lc_batch* b, int32_t stencil) {

@@ -103,6 +103,9 @@ def _load():
         "lc_batch_step": ([ctypes.c_void_p, ctypes.c_int64], ctypes.c_int32),
         "lc_batch_set_tile": ([ctypes.c_void_p, ctypes.c_int32], ctypes.c_int32),
         "lc_batch_set_tiles": ([ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32], ctypes.c_int32),
+        "lc_batch_get_launch": ([ctypes.c_void_p, P(ctypes.c_int32), P(ctypes.c_int32), P(ctypes.c_int32)],
+                                ctypes.c_int32),
+        "lc_batch_set_strips": ([ctypes.c_void_p, ctypes.c_int32], ctypes.c_int32),
         "lc_batch_set_collision": ([ctypes.c_void_p, ctypes.c_int32, P(ctypes.c_double), ctypes.c_int32],
                                    ctypes.c_int32),
         "lc_batch_set_stencil": ([ctypes.c_void_p, ctypes.c_int32], ctypes.c_int32),
@@ -409,6 +412,18 @@ def lc_batch_set_tiles(b, v_lb, v_q):
     _check(_lib.lc_batch_set_tiles(b, int(v_lb), int(v_q)))
 
 
+def lc_batch_get_launch(b):
+    """(strips, v_lb, v_q): whether a step is the marching single pass, and the
+    tile shapes of the two sweeps."""
+    v = [ctypes.c_int32() for _ in range(3)]
+    _check(_lib.lc_batch_get_launch(b, *[ctypes.byref(x) for x in v]))
+    return bool(v[0].value), v[1].value, v[2].value
+
+
+def lc_batch_set_strips(b, strips):
+    _check(_lib.lc_batch_set_strips(b, 1 if strips else 0))
+
+
 def lc_batch_set_stencil(b, stencil):
     _check(_lib.lc_batch_set_stencil(b, int(stencil)))
 
@@ -493,6 +508,12 @@ class BatchSolver:
 
     def set_tiles(self, v_lb, v_q):
         lc_batch_set_tiles(self.b, v_lb, v_q)
+
+    def set_strips(self, strips):
+        lc_batch_set_strips(self.b, strips)
+
+    def launch(self):
+        return lc_batch_get_launch(self.b)
 
     def set_collision(self, kind, rates=()):
         lc_batch_set_collision(self.b, kind, rates)

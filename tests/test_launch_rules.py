@@ -173,3 +173,10 @@ def test_chunks_asked_for_are_cut_evenly(rules, nz, planes, chunk):
     """As many chunks as asked for, none longer, none much shorter."""
     assert rules.rule_even_chunk(nz, planes) == chunk
     assert -(-nz // chunk) == -(-nz // min(planes, nz)) and chunk <= planes
+
+
+def test_batch_launch_needs_a_batch():
+    for call, args in ((lc.lc_batch_get_launch, ()), (lc.lc_batch_set_strips, (1,))):
+        with pytest.raises(lc.LCError) as e:
+            call(None, *args)
+        assert e.value.code == lc.LC_EINVAL
