@@ -481,11 +481,12 @@ lc_status lc_batch_set_stencil(lc_batch *b, int32_t stencil);
  * unknown kind, a wrong count or a rate outside (0, 2). */
 lc_status lc_batch_set_collision(lc_batch *b, int32_t kind, const double *rates, int32_t nrates);
 
-/* Time every pair of tile shapes for trial_steps steps (after one untimed
- * step) with HIP events and keep the fastest; *chosen = v_lb + 7 * v_q.  The
- * marching single pass is timed as well and kept if it is faster than every
- * pair: *ms_per_step is its time then, *chosen still the fastest pair, and
- * lc_batch_get_launch tells which of the two the batch runs.
+/* Time every pair of tile shapes for trial_steps steps (every shape after an
+ * untimed step) with HIP events and keep the fastest; *chosen = v_lb + 7 * v_q.
+ * The marching single pass is timed against that pair, eight steps of a graph
+ * each, and kept if it is faster: *ms_per_step is its time then, *chosen still
+ * the fastest pair, and lc_batch_get_launch tells which of the two the batch
+ * runs.
  * The state advances by 49 * (trial_steps + 1) steps: tune before loading
  * the real state, or load it again afterwards.  Synchronises the stream.
  * Measurement plumbing: implements no passage of the paper. */

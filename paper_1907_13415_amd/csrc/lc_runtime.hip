@@ -1589,15 +1589,11 @@ static void batch_drop_graphs(lc_batch* b) {
   }
 }
 
-// Capture G steps starting from `parity` on the private stream.
-static lc_status batch_build_graph(lc_batch* b, int parity) {
+// Capture n steps starting from `parity` on the private stream.
+static lc_status batch_capture(lc_batch* b, int parity, int n, hipGraph_t* graph, hipGraphExec_t* exec) {
   lc_status st = hip_check(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal), "graph capture begin");
   if (st) return st;
-  int p = parity;
-  for (int i = 0; i < lc_batch::G; i++) {
-    batch_launch_step(b, b->cap, p, i);
-    p ^= 1;
-  }
+  for (int i = 0; i < n; i++) batch_launch_step(b, b->cap, parity ^ (i & 1), i);
   hipGraph_t g = nullptr;
   st = hip_check(hipStreamEndCapture(b->cap, &g), "graph capture end");
   if (st) return st;
@@ -1607,9 +1603,38 @@ static lc_status batch_build_graph(lc_batch* b, int parity) {
     (void)hipGraphDestroy(g);
     return st;
   }
-  b->graph[parity] = g;
-  b->exec[parity] = e;
+  *graph = g;
+  *exec = e;
   return LC_OK;
+}
+
+// The graph of G steps from `parity` on, if there is none yet.
+static lc_status batch_build_graph(lc_batch* b, int parity) {
+  if (b->exec[parity]) return LC_OK;
+  return batch_capture(b, parity, lc_batch::G, &b->graph[parity], &b->exec[parity]);
+}
+
+// n untimed and n timed steps of the batch's present form (n even), each a graph:
+// milliseconds per step.
+static lc_status batch_trial(lc_batch* b, int n, hipEvent_t e0, hipEvent_t e1, float* ms) {
+  hipGraph_t g = nullptr;
+  hipGraphExec_t e = nullptr;
+  lc_status st = batch_capture(b, b->parity, n, &g, &e);
+  if (st) return st;
+  for (int timed = 0; timed < 2 && st == LC_OK; timed++) {
+    st = batch_set_step(b);
+    if (st == LC_OK && timed) st = hip_check(hipEventRecord(e0, b->stream), "event record");
+    if (st == LC_OK) st = hip_check(hipGraphLaunch(e, b->stream), "graph launch");
+    if (st == LC_OK) b->step += n;
+  }
+  if (st == LC_OK) st = hip_check(hipEventRecord(e1, b->stream), "event record");
+  if (st == LC_OK) st = hip_check(hipEventSynchronize(e1), "event sync");
+  if (st == LC_OK) st = hip_check(hipEventElapsedTime(ms, e0, e1), "event time");
+  *ms /= float(n);
+  if (st) (void)hipStreamSynchronize(b->stream);
+  (void)hipGraphExecDestroy(e);
+  (void)hipGraphDestroy(g);
+  return st;
 }
 
 static void batch_sync_views(lc_batch* b) {
@@ -1773,11 +1798,9 @@ lc_status lc_batch_step(lc_batch* b, int64_t n) {
   if (n < 0) return fail(LC_EINVAL, "n must be >= 0");
   if (!b->loaded) return fail(LC_ESTATE, "load every grid of the batch before stepping");
   while (n >= lc_batch::G) {
-    if (!b->exec[b->parity]) {
-      lc_status st = batch_build_graph(b, b->parity);
-      if (st) return st;
-    }
-    lc_status st = batch_set_step(b);
+    lc_status st = batch_build_graph(b, b->parity);
+    if (st) return st;
+    st = batch_set_step(b);
     if (st) return st;
     st = hip_check(hipGraphLaunch(b->exec[b->parity], b->stream), "graph launch");
     if (st) return st;
@@ -1881,14 +1904,21 @@ lc_status lc_batch_autotune(lc_batch* b, int32_t trial_steps, int32_t* chosen, d
     (void)hipEventDestroy(e0);
     return st;
   }
-  // every pair of tile shapes (stress sweep, Q sweep)
+  // Every pair of tile shapes (stress sweep, Q sweep).  One untimed step goes
+  // before the trial of a shape that is new; of the others' untimed steps four
+  // go first, and the rest to the comparison below.
+  const bool strips = b->B.march_tiles > 0;
+  constexpr int OTHERS = (BATCH_NV - 1) * (BATCH_NV - 1), TRIAL = 8;
+  static_assert(OTHERS >= 4 * TRIAL, "the comparison takes two trials of each form");
+  if (strips) st = lc_batch_step(b, OTHERS - 4 * TRIAL);
   int best = 0;
   float best_ms = 1e30f;
   for (int v = 0; v < BATCH_NV * BATCH_NV && st == LC_OK; v++) {
     st = lc_batch_set_tiles(b, v % BATCH_NV, v / BATCH_NV);
     if (st) break;
-    // one untimed step, then the timed trial
-    st = lc_batch_step(b, 1);
+    if (!strips || v % BATCH_NV == 0 || v / BATCH_NV == 0) st = lc_batch_step(b, 1);
+    // no graph left to build in the trial
+    if (st == LC_OK && trial_steps >= lc_batch::G) st = batch_build_graph(b, b->parity);
     if (st) break;
     (void)hipEventRecord(e0, b->stream);
     st = lc_batch_step(b, trial_steps);
@@ -1903,36 +1933,25 @@ lc_status lc_batch_autotune(lc_batch* b, int32_t trial_steps, int32_t* chosen, d
       best = v;
     }
   }
-  // the marching single pass: the same step again and again, from the current
-  // state into the other buffers, so that the state does not move
-  bool march = false;
-  if (st == LC_OK && b->B.march_tiles) {
-    b->march = true;
-    float ms = 0;
-    st = batch_set_step(b);
-    batch_launch_step(b, b->stream, b->parity, 0);
-    (void)hipEventRecord(e0, b->stream);
-    for (int i = 0; i < trial_steps; i++) batch_launch_step(b, b->stream, b->parity, 0);
-    (void)hipEventRecord(e1, b->stream);
-    if (st == LC_OK) st = hip_check(hipEventSynchronize(e1), "event sync");
-    if (st == LC_OK) {
-      (void)hipEventElapsedTime(&ms, e0, e1);
-      march = ms < best_ms;
-      best_ms = std::min(ms, best_ms);
+  best_ms /= float(trial_steps);
+  if (st == LC_OK) st = lc_batch_set_tiles(b, best % BATCH_NV, best / BATCH_NV);
+  // the best pair and the marching single pass under the same conditions
+  if (st == LC_OK && strips) {
+    float ms[2] = {0, 0};
+    for (int form = 0; form < 2 && st == LC_OK; form++) {
+      b->march = form == 1;
+      st = batch_trial(b, TRIAL, e0, e1, &ms[form]);
     }
-    b->march = false;
+    b->march = st == LC_OK && ms[1] < ms[0];
+    if (b->march) best_ms = ms[1];
+    batch_drop_graphs(b);
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (st) return st;
   if (chosen) *chosen = best;
-  if (ms_per_step) *ms_per_step = double(best_ms) / trial_steps;
-  st = lc_batch_set_tiles(b, best % BATCH_NV, best / BATCH_NV);
-  if (st == LC_OK && march) {
-    b->march = true;
-    batch_drop_graphs(b);
-  }
-  return st;
+  if (ms_per_step) *ms_per_step = double(best_ms);
+  return LC_OK;
 }
 
 lc_status lc_batch_observe(lc_batch* b, uint32_t mask, int32_t half_axis, lc_observables* out) {

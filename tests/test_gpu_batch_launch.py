@@ -65,3 +65,20 @@ def test_tuned_launch_carries_over(shapes):
     a.step(66)
     b.step(66)
     assert all(np.array_equal(x, y) for x, y in zip(_state(lc, a), _state(lc, b)))
+
+
+@pytest.mark.parametrize("precision,trial", [("fp32sr", 3), ("fp64", 64), ("fp32dev", 70)])
+def test_tuning_advances_the_state_by_its_trials(precision, trial):
+    """49 times (trial + 1) steps, also with trials that replay graphs, and none
+    for the strips: the state is that of as many plain steps."""
+    require_gpu()
+    from paper_1907_13415_amd import lc
+    print("tuning state %s %d" % (precision, trial), flush=True)
+    a, b = _batch(lc, SMALL, precision), _batch(lc, SMALL, precision)
+    a.autotune(trial)
+    b.step(49 * (trial + 1))
+    assert a.observe()[0]["step"] == 49 * (trial + 1)
+    assert all(np.array_equal(x, y) for x, y in zip(_state(lc, a), _state(lc, b)))
+    a.step(67)
+    b.step(67)
+    assert all(np.array_equal(x, y) for x, y in zip(_state(lc, a), _state(lc, b)))
