@@ -354,7 +354,11 @@ lc_status lc_sync(lc_ctx *ctx);
  * HIP events on the context stream around each launch of the split and
  * fused variants (every 1024 launches the context waits for the recorded
  * ones and folds them into running sums, so the number of events it holds
- * stays bounded).  lc_get_timing synchronises, returns the summed
+ * stays bounded).  Every timed launch belongs to one step: D2Q9 grids of at
+ * most 256 tiles of 16x8 sites, which otherwise take two steps per launch of
+ * the single pass, take one while timing is enabled (the same results), so
+ * their times are a little above those of untimed steps.  lc_get_timing
+ * synchronises, returns the summed
  * durations in milliseconds and the number of launches of kind 0 (the
  * stress/LB sweep, or the single pass of the fused variant) and kind 1 (the
  * Q sweep) since the last call, and resets the record.  Measurement plumbing:
