@@ -207,20 +207,40 @@ inline Form2d fused2d_form(const lc_grid& g, bool isotropic, bool timed) {
   return FORM_TILES;
 }
 
+// Whether the tiles of the single pass are expected to take at most as long as
+// the two sweeps on a grid with more tiles than CUs, below the strips' sites: the
+// tiles go through the chip in rounds, a part of a round at `part` of a whole one
+// at least; the sweeps' time grows with their blocks of 32x8 sites.  Fitted to
+// 2184 measured grids of 70 000 to 405 000 sites (1 to 600 rows or columns),
+// tiles / sweeps: Q float 0.55 to 0.96 in two rounds (512^2 FP32 10.7 and 13.5
+// us), 0.61 to 1.15 in three and four, 0.83 to 1.76 in more (300000x1 1.67); Q
+// double 0.58 to 1.16 in two rounds (448^2 FP64 18.8 and 18.4 us, 33x4454 0.87),
+// 0.74 to 1.35 in three and four, up to 2.2 in more.  On average the choice costs
+// 0.2% over the faster one (0.6% in FP32), at most 19%.
+inline bool tiles_beat_sweeps(const lc_grid& g) {
+  const bool dq = double_q(g);
+  const double launch = dq ? 0.20 : -0.09, part = dq ? 0.61 : 0.62, block = (dq ? 1.54 : 2.64) / 1024;
+  const double round[2][FUSED2D_NV] = {{0.93, 0.93, 1.13, 1.44, 1.67}, {0.74, 0.74, 0.90, 1.10, 1.25}};  // by shape
+  const int v = fused2d_shape(g);
+  const double tiles = double(fused2d_tiles(g, v)) / NUM_CU, full = double(int64_t(tiles)), rest = tiles - full;
+  const double rounds = full + (rest > 0.0 ? part + (1.0 - part) * rest : 0.0);
+  const double blocks = double((g.nx + 31) / 32) * ((g.ny + 7) / 8);
+  return launch + round[dq][v] * rounds <= 1.0 + block * blocks;
+}
+
 // The variant AUTO runs (bit-identical results).  The two sweeps in 3D.  In 2D
 // the single pass, in tiles where each has a CU of its own (launches are
 // latency bound there: 256^2 5.6 us per step in FP32 against 9.0 in two sweeps,
 // 7.1 against 10.0 in FP64; 384^2 8.0 against 11.1 and 11.5 against 14.7),
-// marching on large grids (march_takes) unless the sweeps are faster there
-// (march_beats_sweeps); in between, up to 640^2 sites, in tiles where Q is float (512^2 12.0 against 13.3 us, with the isotropic
-// stencils 14.9 against 16.3), and the two sweeps elsewhere (448^2 in FP64
-// 18.7 against 20.5 us, mixed 16.2 against 17.6).
+// marching on large grids; it or the two sweeps, whichever is expected to be
+// faster, in between and where the strips are many.
 inline int auto_variant(const lc_grid& g, bool isotropic) {
   if (g.lattice != LC_D2Q9) return LC_VARIANT_SPLIT;
-  if (fused2d_fits(g) || (march_takes(1, &g) && march_beats_sweeps(1, &g, isotropic)) ||
-      (!double_q(g) && int64_t(g.nx) * g.ny < MARCH_MIN_SITES))
-    return LC_VARIANT_FUSED;
-  return LC_VARIANT_SPLIT;
+  if (fused2d_fits(g)) return LC_VARIANT_FUSED;
+  const bool single = int64_t(g.nx) * g.ny < MARCH_MIN_SITES
+                          ? tiles_beat_sweeps(g)
+                          : march_takes(1, &g) && march_beats_sweeps(1, &g, isotropic);
+  return single ? LC_VARIANT_FUSED : LC_VARIANT_SPLIT;
 }
 
 // Tiles of the reverse step (lc_vjp.h), one block of REV_NTHR threads each:

@@ -61,9 +61,16 @@ def test_steps_that_are_not_paired(rules):
 
 @pytest.mark.parametrize("precision,nx,ny,variant", [
     ("fp64", 400, 380, lc.LC_VARIANT_FUSED), ("fp64", 448, 448, lc.LC_VARIANT_SPLIT),
-    ("mixed", 448, 448, lc.LC_VARIANT_SPLIT), ("fp32dev", 448, 448, lc.LC_VARIANT_FUSED),
+    ("fp32dev", 448, 448, lc.LC_VARIANT_FUSED),
     ("fp32sr", 639, 640, lc.LC_VARIANT_FUSED), ("fp64", 640, 640, lc.LC_VARIANT_FUSED),
-    ("fp64", 639, 640, lc.LC_VARIANT_SPLIT), ("fp32dev", 64, 7000, lc.LC_VARIANT_SPLIT)])
+    ("fp64", 639, 640, lc.LC_VARIANT_SPLIT), ("fp32dev", 64, 7000, lc.LC_VARIANT_SPLIT),
+    # more tiles than CUs: full and nearly empty rounds, tiles of one row, narrow grids
+    ("fp32dev", 512, 512, lc.LC_VARIANT_FUSED), ("fp64", 512, 512, lc.LC_VARIANT_FUSED),
+    ("mixed", 400, 400, lc.LC_VARIANT_FUSED), ("fp64", 742, 256, lc.LC_VARIANT_SPLIT),
+    ("fp32sr", 120000, 1, lc.LC_VARIANT_SPLIT), ("fp32dev", 300000, 1, lc.LC_VARIANT_SPLIT),
+    ("fp64", 11111, 9, lc.LC_VARIANT_FUSED), ("mixed", 10000, 2, lc.LC_VARIANT_FUSED),
+    ("fp64", 33, 4454, lc.LC_VARIANT_FUSED), ("mixed", 16, 9187, lc.LC_VARIANT_FUSED),
+    ("fp32dev", 8, 37500, lc.LC_VARIANT_FUSED), ("fp64", 29400, 5, lc.LC_VARIANT_SPLIT)])
 def test_auto_variant_at_its_thresholds(rules, precision, nx, ny, variant):
     assert rules.rule_auto_variant(ref(grid2d(nx, ny, precision)), 0) == variant
 
