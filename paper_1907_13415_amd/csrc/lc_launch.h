@@ -59,7 +59,11 @@ inline int even_chunk(int nz, int planes) {
 // Measured on the stress/LB and Q sweeps, long default chunks against the
 // chosen ones: 24^3 FP32 67.7 -> 14.7 and 56.9 -> 11.7 us, 64^3 FP64
 // 80 -> 32 and 147 -> 24 us, 129x100x75 FP32 isotropic 186 -> 95 and
-// 474 -> 111 us; from 256^3 on the chunk is the longest allowed.
+// 474 -> 111 us.  On large grids it stays near the longest: 16 of 16 and 86 of
+// 128 planes on 256^3, 15 and 54 on 270^3 (FP32).
+// `resident` is what the sweep's registers and LDS allow on a CU: two blocks of
+// the stress/LB sweep, three of the Q sweep (two with the isotropic stencils),
+// one of the single pass; a kernel that changes those needs it changed.
 // `margin`: chunks that make more blocks than the longest do must be estimated
 // that much faster; the longest are at least cut evenly.
 inline int pick_chunk(int nz, int64_t tiles, int most, int extra, int resident = 2, double margin = 0.0) {
@@ -116,9 +120,10 @@ inline int64_t march_strips(const lc_grid& g) { return (g.nx + MARCH_COLS - 1) /
 
 // Waves of the march that the chip holds at once: two per SIMD where Q is
 // float, one where it is double (the registers set it).  Chunks are cut so
-// that a launch has at most that many, in one round; measured per step on
-// 2048^2 sites, FP32: 130 us with 1998 waves of 38 rows, 160 with 2368 waves
-// of 32 rows (a second round for the rest), 178 with 814 waves of 96 rows.
+// that a launch has at most that many, in one round, unless the strips alone are
+// more; measured per step on 2048^2 sites, FP32: 130 us with 1998 waves of 38
+// rows, 160 with 2368 waves of 32 rows (a second round for the rest), 178 with
+// 814 waves of 96 rows.
 constexpr int march_waves(bool double_q) { return (double_q ? 4 : 8) * NUM_CU; }
 inline bool double_q(const lc_grid& g) { return g.precision == LC_FP64 || g.precision == LC_MIXED; }
 
@@ -147,11 +152,11 @@ inline int march_rows(int n, const lc_grid* g) {
 // Whether the marching single pass takes n 2D grids (one, or the grids of a
 // batch) of at least MARCH_MIN_SITES sites together.  Below that its waves
 // have too few rows each to be worth the eight they repeat: 512^2 in FP32
-// 15.0 us per step against 11.6 in tiles and 13.4 in two sweeps, in FP64 24.1
-// against 21.7 and 22.8; 700^2 20.0 against 24.7 in two sweeps, and 32.7
-// against 38.9; 1400^2 46.6 against 80.7, and 125 against 150.  A strip is 56
+// 15.0 us per step against 10.7 in tiles and 13.5 in two sweeps, in FP64 24.1
+// against 19.8 and 20.2; 700^2 18.0 against 21.2 in two sweeps, and 28.4
+// against 32.7; 1000^2 27.1 against 35.9, and 45.7 against 58.8.  A strip is 56
 // columns wide: grids that fill less than three quarters of their strips stay
-// in tiles, and so do components beyond 32-bit byte offsets.
+// in the other forms, and so do components beyond 32-bit byte offsets.
 constexpr int64_t MARCH_MIN_SITES = 640 * 640;
 inline bool march_offsets_fit(int n, const lc_grid* g) {
   for (int k = 0; k < n; k++)

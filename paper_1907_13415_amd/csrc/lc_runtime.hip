@@ -364,7 +364,7 @@ static void step_split_ptrs(lc_ctx* c, hipStream_t st, bool mark, const Chunks& 
       ctx_end(c, st, e, 0);
       e = mark ? ctx_begin(c, st) : nullptr;
       // the 3D float Q sweep with these stencils is held to two waves per
-      // SIMD (some registers spill; measured 12% faster than one wave)
+      // SIMD (16 registers spill; one wave was 12% slower when 42 spilled)
       constexpr int IQW = (C::d3 && sizeof(QT) == 4) ? 2 : C::Q_WPE;
       hipLaunchKernelGGL((split_q<LAT, QT, C::Q_TX, C::Q_TY, IQW, false, STENCIL_ISO>), g2,
                          dim3(C::Q_TX, C::Q_TY), 0, st, q0, u, q1, gd, kq, zc2, rec_q, 0u, stream_q);

@@ -323,10 +323,12 @@ __device__ __forceinline__ void q_update(uint32_t s, const Sym<S>& q, const Sym<
   }
 }
 
-// The same into memory.  STREAM: nontemporal stores, for tiles whose rows are
-// whole cache lines; the strips of lc_march2d.h share their first and last
-// lines with their neighbours and leave them in the cache to be completed
-// (1400^2 in FP32: 46.6 us per step against 58.0 with nontemporal stores).
+// The same into memory.  STREAM: nontemporal stores, which the sweeps choose by
+// the grid (store_site).  The 2D tiles and the 3D single pass store so at any
+// width (plain stores of f in tiles: 250x333 3% slower); the strips of
+// lc_march2d.h share their first and last lines with their neighbours and leave
+// them in the cache to be completed (1400^2 in FP32: 46.6 us per step against
+// 58.0 with nontemporal stores).
 template <typename S, bool SR, bool STREAM = true>
 __device__ __forceinline__ void store_q_update(S* __restrict__ Qout, int64_t N, int64_t s, const Sym<S>& q,
                                                const Sym<S>& r, const Sym<S>& rp, uint32_t srkey) {
@@ -682,7 +684,7 @@ __device__ __forceinline__ void split_q_body(const S* __restrict__ Qin, const S*
   // waves per CU; FP64, which held Q^P in three LDS planes, 296 -> 242
   // registers and 67.7 -> 53.3 KB, two -> three blocks of two waves.
   // Sweep on 256^3: FP32 337 -> 327 us, FP32 SR 396 -> 370, FP64 697 -> 656,
-  // FP32 isotropic (no spills now) 1019 -> 683; 200x180x150: FP32 145 -> 136,
+  // FP32 isotropic (16 registers still spill) 1019 -> 683; 200x180x150: FP32 145 -> 136,
   // FP64 274 -> 238.
   // isotropic stencils: the predictor also runs at the ring's corners, and
   // in 3D the corrector reads the predictor's diagonal neighbours in the
