@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <exception>
 #include <mutex>
 #include <new>
 #include <string>
@@ -32,8 +33,23 @@ lc_status fail(lc_status code, const char* fmt, ...) {
   va_start(ap, fmt);
   vsnprintf(buf, sizeof buf, fmt, ap);
   va_end(ap);
-  g_err = buf;
+  try {
+    g_err = buf;
+  } catch (...) {  // no memory for the message
+    g_err.clear();
+  }
   return code;
+}
+
+// What the body of an entry point that allocates on the host returns; a failed
+// allocation is a status, for no exception may leave the C interface.
+template <typename BODY>
+static lc_status no_throw(BODY body) {
+  try {
+    return body();
+  } catch (const std::exception&) {
+    return fail(LC_ENOMEM, "host allocation failed");
+  }
 }
 
 lc_status hip_check(hipError_t e, const char* what) {
@@ -860,7 +876,7 @@ lc_status lc_step(lc_ctx* c, int64_t n) {
   if (n < 0) return fail(LC_EINVAL, "n must be >= 0");
   if (!c->loaded) return fail(LC_ESTATE, "lc_step before lc_load_state");
   if (n == 0) return LC_OK;
-  return LC_DISPATCH(c, run_steps, n);
+  return no_throw([&] { return LC_DISPATCH(c, run_steps, n); });  // (timing records events)
 }
 
 lc_status lc_observe(lc_ctx* c, uint32_t mask, int32_t half_axis, lc_observables* out) {
@@ -1176,7 +1192,7 @@ lc_status lc_get_timing(lc_ctx* c, double* ms, int64_t* launches) {
   launches[0] = launches[1] = 0;
   lc_status st = hip_check(hipStreamSynchronize(c->stream), "timing sync");
   if (st) return st;
-  st = ctx_fold(c);
+  st = no_throw([&] { return ctx_fold(c); });
   if (st) return st;
   for (int k = 0; k < 2; k++) {
     ms[k] = c->acc_ms[k];
@@ -1414,7 +1430,7 @@ struct lc_batch {
   std::vector<lc_params> params;
   lc_buffers arena;
   hipStream_t stream;
-  hipStream_t cap;  // private stream used only to capture graphs
+  hipStream_t cap = nullptr;  // private stream used only to capture graphs
   BatchLayout B;
   std::vector<lc_ctx> views;  // single-grid contexts over the arenas
   std::vector<char> host_desc;
@@ -1637,39 +1653,9 @@ static lc_status batch_trial(lc_batch* b, int n, hipEvent_t e0, hipEvent_t e1, f
   return st;
 }
 
-static void batch_sync_views(lc_batch* b) {
-  for (auto& v : b->views) {
-    v.parity = b->parity;
-    v.step = b->step;
-  }
-}
-
-}  // namespace lc
-
-extern "C" {
-
-lc_status lc_batch_layout(int32_t ngrids, const lc_grid* grids, size_t* f_bytes, size_t* q_bytes,
-                          size_t* scratch_bytes, size_t* f_offsets, size_t* q_offsets) {
-  clear_error();
-  BatchLayout B;
-  lc_status st = batch_layout_of(ngrids, grids, B);
-  if (st) return st;
-  if (f_bytes) *f_bytes = B.f_bytes;
-  if (q_bytes) *q_bytes = B.q_bytes;
-  if (scratch_bytes) *scratch_bytes = B.scratch_bytes;
-  for (int k = 0; k < ngrids; k++) {
-    if (f_offsets) f_offsets[k] = B.f_off[k];
-    if (q_offsets) q_offsets[k] = B.q_off[k];
-  }
-  return LC_OK;
-}
-
-lc_status lc_batch_init(int32_t ngrids, const lc_grid* grids, const lc_params* params, const lc_buffers* arena,
-                        void* stream, lc_batch** out) {
-  clear_error();
-  if (!out) return fail(LC_EINVAL, "out is NULL");
-  *out = nullptr;
-  if (!params || !arena) return fail(LC_EINVAL, "NULL argument");
+// The batch, in *out as soon as it exists: on failure the caller destroys it.
+static lc_status batch_create(int32_t ngrids, const lc_grid* grids, const lc_params* params, const lc_buffers* arena,
+                              void* stream, lc_batch** out) {
   BatchLayout B;
   lc_status st = batch_layout_of(ngrids, grids, B);
   if (st) return st;
@@ -1684,6 +1670,7 @@ lc_status lc_batch_init(int32_t ngrids, const lc_grid* grids, const lc_params* p
   }
   lc_batch* b = new (std::nothrow) lc_batch;
   if (!b) return fail(LC_ENOMEM, "batch allocation failed");
+  *out = b;
   b->n = ngrids;
   b->grids.assign(grids, grids + ngrids);
   b->params.assign(params, params + ngrids);
@@ -1700,10 +1687,7 @@ lc_status lc_batch_init(int32_t ngrids, const lc_grid* grids, const lc_params* p
     b->graph[p] = nullptr;
   }
   st = hip_check(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking), "capture stream");
-  if (st) {
-    delete b;
-    return st;
-  }
+  if (st) return st;
   char* scr = static_cast<char*>(arena->scratch);
   b->views.resize(ngrids);
   for (int k = 0; k < ngrids; k++) {
@@ -1737,11 +1721,7 @@ lc_status lc_batch_init(int32_t ngrids, const lc_grid* grids, const lc_params* p
     st = hip_check(hipMemcpyAsync(scr + B.off_map[vv], b->host_map[vv].data(), b->host_map[vv].size() * sizeof(int),
                                   hipMemcpyHostToDevice, b->stream),
                    "tile map upload");
-    if (st) {
-      (void)hipStreamDestroy(b->cap);
-      delete b;
-      return st;
-    }
+    if (st) return st;
   }
   for (int k = 0; k < ngrids; k++) {
     const int t1 = k + 1 < ngrids ? B.march0[k + 1] : B.march_tiles;
@@ -1752,20 +1732,56 @@ lc_status lc_batch_init(int32_t ngrids, const lc_grid* grids, const lc_params* p
                                   hipMemcpyHostToDevice, b->stream),
                    "strip map upload");
   if (st == LC_OK) st = batch_upload(b);
-  if (st) {
-    (void)hipStreamDestroy(b->cap);
-    delete b;
-    return st;
-  }
+  if (st) return st;
   // the host tables must stay valid until the uploads have run
-  st = hip_check(hipStreamSynchronize(b->stream), "batch init sync");
-  if (st) {
-    (void)hipStreamDestroy(b->cap);
-    delete b;
-    return st;
+  return hip_check(hipStreamSynchronize(b->stream), "batch init sync");
+}
+
+static void batch_sync_views(lc_batch* b) {
+  for (auto& v : b->views) {
+    v.parity = b->parity;
+    v.step = b->step;
   }
-  *out = b;
+}
+
+}  // namespace lc
+
+extern "C" {
+
+lc_status lc_batch_layout(int32_t ngrids, const lc_grid* grids, size_t* f_bytes, size_t* q_bytes,
+                          size_t* scratch_bytes, size_t* f_offsets, size_t* q_offsets) {
+  clear_error();
+  BatchLayout B;
+  lc_status st = no_throw([&] { return batch_layout_of(ngrids, grids, B); });
+  if (st) return st;
+  if (f_bytes) *f_bytes = B.f_bytes;
+  if (q_bytes) *q_bytes = B.q_bytes;
+  if (scratch_bytes) *scratch_bytes = B.scratch_bytes;
+  for (int k = 0; k < ngrids; k++) {
+    if (f_offsets) f_offsets[k] = B.f_off[k];
+    if (q_offsets) q_offsets[k] = B.q_off[k];
+  }
   return LC_OK;
+}
+
+lc_status lc_batch_init(int32_t ngrids, const lc_grid* grids, const lc_params* params, const lc_buffers* arena,
+                        void* stream, lc_batch** out) {
+  clear_error();
+  if (!out) return fail(LC_EINVAL, "out is NULL");
+  *out = nullptr;
+  if (!params || !arena) return fail(LC_EINVAL, "NULL argument");
+  lc_batch* b = nullptr;
+  const lc_status st = no_throw([&] { return batch_create(ngrids, grids, params, arena, stream, &b); });
+  if (st == LC_OK) {
+    *out = b;
+  } else if (b) {
+    if (b->cap) {
+      (void)hipStreamSynchronize(b->stream);  // uploads from the batch's tables may be under way
+      (void)hipStreamDestroy(b->cap);
+    }
+    delete b;
+  }
+  return st;
 }
 
 lc_status lc_batch_load_state(lc_batch* b, int32_t k, const double* f_dev, const double* q_dev) {
@@ -1966,8 +1982,13 @@ lc_status lc_batch_observe(lc_batch* b, uint32_t mask, int32_t half_axis, lc_obs
     lc_status st = LC_DISPATCH(c, do_observe_async, mask, half_axis, res + size_t(k) * OBS_W);
     if (st) return st;
   }
-  std::vector<double> h(size_t(b->n) * OBS_W);
-  lc_status st = hip_check(hipMemcpyAsync(h.data(), res, h.size() * sizeof(double), hipMemcpyDeviceToHost, b->stream),
+  std::vector<double> h;
+  lc_status st = no_throw([&] {
+    h.resize(size_t(b->n) * OBS_W);
+    return LC_OK;
+  });
+  if (st) return st;
+  st = hip_check(hipMemcpyAsync(h.data(), res, h.size() * sizeof(double), hipMemcpyDeviceToHost, b->stream),
                            "batch observe copy");
   if (st) return st;
   st = hip_check(hipStreamSynchronize(b->stream), "batch observe sync");
